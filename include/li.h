@@ -64,7 +64,7 @@ enum {
 };
 
 typedef enum {
-    LI_FP32 = 0,   /* FP32 operands, FP32 matrix-core products           */
+    LI_FP32 = 0,   /* FP32 operands, products and sums                   */
     LI_BF16 = 1,   /* operands rounded to bfloat16 (nearest-even)        */
     LI_FP16 = 2,   /* operands rounded to binary16 (nearest-even)        */
     LI_BF16X3 = 3  /* split bf16: X = Xh + Xl, Ah*Bh + Ah*Bl + Al*Bh     */
@@ -83,7 +83,11 @@ li_status li_init(void);
 /* GEMM (Sec. VI-C listing of the matrix multiply; polybench GEMM, Sec. VIII):
  *   C = alpha * A * B + beta * C
  * A: M x K, B: K x N, C: M x N, FP32 device pointers.  C must not overlap A
- * or B.  FP32 matrix-core products with FP32 accumulation. */
+ * or B.  FP32 products with FP32 accumulation: on the FP32 matrix cores, or
+ * (main-loop modes 9 to 11 below) on the bf16 matrix cores from operands
+ * split exactly into three bf16 parts, whose result is at least as close to
+ * the exact one; infinities, NaN, subnormal and other values that the parts
+ * cannot hold give what the FP32 cores give. */
 li_status li_gemm(int64_t M, int64_t N, int64_t K, float alpha, const float *A,
                   const float *B, float beta, float *C, li_stream stream);
 
@@ -339,7 +343,10 @@ typedef struct li_tile_config {
                                8: direct HBM-to-LDS loads into a two-stage
                                ring (mode 4 when K is not a multiple of
                                the K-tile, mode 2 where three stages do
-                               not fit in LDS).  LI_KERNEL_GEMM_LP: the LDS
+                               not fit in LDS); 9, 10, 11: operands split
+                               into three bf16 parts by 4, 2 or 8 further
+                               waves, six part products on the bf16 matrix
+                               cores.  LI_KERNEL_GEMM_LP: the LDS
                                layout instead (1: XOR-swizzled rows, 2:
                                padded rows, 3: layout 1 filled by direct
                                HBM-to-LDS loads, 4: 3 with the next k

@@ -288,6 +288,14 @@ struct F32Tile {
                   "fused centring needs k-major operands");
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_;
     static constexpr int NT = 64 * WM * WN;
+    // Threads that hold the result after the main loop (here all of them; see
+    // SplitTile), and whether this is one of them.
+    static constexpr int ET = NT;
+    __device__ __forceinline__ static bool active() { return true; }
+    static constexpr bool SPLIT = false;
+    // work-groups of a stream-K grid per compute unit: as many as are
+    // resident at once
+    static constexpr int SK_PER_CU = NT >= 1024 ? 1 : 2;
     static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     static_assert(TM >= 1 && TN >= 1 && BM % (32 * WM) == 0 && BN % (32 * WN) == 0, "bad wave tiling");
     static_assert(BK % 8 == 0, "BK must be a multiple of 8");
@@ -1274,6 +1282,20 @@ struct F32Tile {
                         C[row * ldc + col] = combine(alpha, acc[tm][tn][v], beta, cv[tm][tn][v]);
                 }
             }
+    }
+
+    // C = alpha*acc + beta*C; with beta != 0 the tile's C loads are issued
+    // together, then one wait (not a load-wait-store round trip per element)
+    __device__ __forceinline__ static void store_c(const f32x16 (&acc)[TM][TN], float *C, int64_t ldc, int64_t M,
+                                                   int64_t N, int64_t m0, int64_t n0, float alpha, float beta)
+    {
+        if (beta != 0.f) {
+            float cv[TM][TN][16];
+            load_c(cv, C, ldc, M, N, m0, n0);
+            epilogue_gemm_loaded(acc, cv, C, ldc, M, N, m0, n0, alpha, beta);
+        } else {
+            epilogue_gemm(acc, C, ldc, M, N, m0, n0, alpha, 0.f);
+        }
     }
 
     // Symmetric result S (M x M): the tile at (m0, n0) with n0 >= m0 writes

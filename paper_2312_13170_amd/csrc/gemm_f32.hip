@@ -5,6 +5,7 @@
 
 #include "f32_tile.h"
 #include "li_internal.h"
+#include "split_tile.h"
 #include "symm_kernels.h"
 #include "tiles.h"
 
@@ -30,15 +31,7 @@ __global__ __launch_bounds__(T::NT) void gemm_f32_kernel(const float *__restrict
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
     if (alpha != 0.f) T::mainloop(lds, A, lda, B, ldb, M, N, 0, K, m0, n0, acc);
-    if (beta != 0.f) {
-        // all of the tile's C loads issued together, then one wait (not a
-        // load-wait-store round trip per element)
-        float cv[T::TM][T::TN][16];
-        T::load_c(cv, C, ldc, M, N, m0, n0);
-        T::epilogue_gemm_loaded(acc, cv, C, ldc, M, N, m0, n0, alpha, beta);
-    } else {
-        T::epilogue_gemm(acc, C, ldc, M, N, m0, n0, alpha, 0.f);
-    }
+    if (T::active()) T::store_c(acc, C, ldc, M, N, m0, n0, alpha, beta);
 }
 
 template <class T>
@@ -54,7 +47,39 @@ int run_gemm(int64_t M, int64_t N, int64_t K, float alpha, const float *A, int64
     return (int)hipGetLastError();
 }
 
+// a candidate of the FP32 cores that takes every shape
+constexpr int kGemmF32Plain = 18;
+
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
+// One candidate of the list.  Prefetch modes 5-7 are modes 1-3 with B
+// transposed into LDS; the direct-to-LDS modes (4: three-stage ring, 8:
+// two-stage ring) need 16-byte rows and fall back to mode 2 otherwise; mode 8
+// runs as mode 4 (which takes a ragged last K-tile; mode 2 where three stages
+// do not fit in LDS) when K is not a multiple of the K-tile.  Modes 9 to 11
+// are the split tiles; rows too long for their 32-bit offsets take the FP32
+// cores.
+template <int BM, int BN, int BK, int WM, int WN, int PF>
+int run_gemm_candidate(bool v4, int64_t M, int64_t N, int64_t K, float alpha, const float *A, int64_t lda,
+                       const float *B, int64_t ldb, float beta, float *C, int64_t ldc, hipStream_t s)
+{
+#define LI_RUN(LOAD, MODE, TR) \
+    run_gemm<F32Tile<BM, BN, BK, WM, WN, false, LOAD, MODE, false, 0, TR>>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s)
+    if constexpr (PF >= 9) {
+        using T = SplitTile<BM, BN, BK, WM, WN, split_waves(PF), true, false, false>;
+        if (lda > kSplitMaxLd || ldb > kSplitMaxLd)
+            return launch_gemm_f32(kGemmF32Plain, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+        return run_gemm<T>(M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+    } else {
+        constexpr bool TR = PF > 4 && PF < 8;
+        constexpr int MODE = TR ? PF - 4 : PF;
+        // the three-stage ring when it fits in LDS, else the register path
+        constexpr int RAGGED = PF == 8 ? ((BM + BN) * BK * 4 * 3 <= 160 * 1024 ? 4 : 2) : MODE;
+        if (!v4) return LI_RUN(kLoadScalar, (PF == 4 || PF == 8 ? 2 : MODE), TR);
+        return PF != 8 || K % BK == 0 ? LI_RUN(kLoadVec4, MODE, TR) : LI_RUN(kLoadVec4, RAGGED, TR);
+    }
+#undef LI_RUN
+}
 
 // ---------------------------------------------------------- stream-K GEMM
 // The nb output tiles times kt K-tiles form one iteration space split
@@ -192,28 +217,11 @@ int launch_gemm_f32(int cfg, int64_t M, int64_t N, int64_t K, float alpha, const
     const bool v4 = (alpha == 0.f || (K % 4 == 0 && N % 4 == 0 && lda % 4 == 0 && ldb % 4 == 0 &&
                                       aligned16(A) && aligned16(B)));
     switch (cfg) {
-// prefetch modes 5-7 are modes 1-3 with B transposed into LDS; the
-// direct-to-LDS modes (4: three-stage ring, 8: two-stage ring) need 16-byte
-// rows and fall back to mode 2 otherwise; mode 8 runs as mode 4 (which
-// takes a ragged last K-tile; mode 2 where three stages do not fit in LDS)
-// when K is not a multiple of the K-tile
-// the three-stage ring when it fits in LDS, else the register path
-#define LI_RAGGED_DMA(BM, BN, BK) ((BM + BN) * BK * 4 * 3 <= 160 * 1024 ? 4 : 2)
-#define LI_T(BM, BN, BK, WM, WN, LOAD, PF) \
-    F32Tile<BM, BN, BK, WM, WN, false, LOAD, (PF > 4 && PF < 8 ? PF - 4 : PF), false, 0, (PF > 4 && PF < 8)>
-#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF)                                                     \
-    case IDX:                                                                                      \
-        return v4 && (PF != 8 || K % BK == 0)                                                      \
-                   ? run_gemm<LI_T(BM, BN, BK, WM, WN, kLoadVec4, PF)>(M, N, K, alpha, A, lda, B, ldb, \
-                                                                      beta, C, ldc, s)             \
-                   : v4 ? run_gemm<LI_T(BM, BN, BK, WM, WN, kLoadVec4, (PF == 8 ? LI_RAGGED_DMA(BM, BN, BK) : PF))>( \
-                              M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s)                     \
-                        : run_gemm<LI_T(BM, BN, BK, WM, WN, kLoadScalar, (PF == 4 || PF == 8 ? 2 : PF))>( \
-                              M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
+#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF) \
+    case IDX:                                    \
+        return run_gemm_candidate<BM, BN, BK, WM, WN, PF>(v4, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, s);
         LI_GEMM_F32_CANDIDATES(LI_CASE)
 #undef LI_CASE
-#undef LI_T
-#undef LI_RAGGED_DMA
     default:
         return (int)hipErrorInvalidValue;
     }

@@ -45,6 +45,8 @@ struct TileCfg {
 };
 int tune_num(int kernel);
 const TileCfg &tune_cfg(int kernel, int idx);
+// table slot of a call
+int tune_key(int kernel, int64_t M, int64_t N, int64_t K);
 // candidate index for a problem: forced > table > built-in heuristic
 int tune_pick(int kernel, int64_t M, int64_t N, int64_t K);
 

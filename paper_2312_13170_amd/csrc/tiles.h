@@ -8,6 +8,9 @@
 // (symmetric contractions only).  prefetch: main-loop mode 1-4; in the FP32
 // GEMM list 5-7 are modes 1-3 with B transposed into LDS and 8 is the
 // direct-to-LDS loop with a two-stage ring (K a multiple of the K-tile).
+// 9, 10, 11: operands split into three bf16 parts, multiplied on the bf16
+// matrix cores (split_tile.h), with 4, 2 and 8 splitting waves beside the
+// waves_m x waves_n matrix waves.
 #define LI_GEMM_F32_CANDIDATES(X)            \
     X(0, 128, 128, 32, 2, 2, 1, 1)           \
     X(1, 128, 128, 16, 2, 2, 1, 1)           \
@@ -59,7 +62,12 @@
     X(47, 256, 128, 32, 4, 2, 1, 4)          \
     X(48, 256, 128, 32, 4, 2, 1, 8)          \
     X(49, 128, 256, 32, 2, 4, 1, 8)          \
-    X(50, 32, 32, 32, 1, 1, 1, 3)
+    X(50, 32, 32, 32, 1, 1, 1, 3)            \
+    X(51, 128, 128, 32, 2, 2, 1, 9)          \
+    X(52, 64, 64, 32, 2, 2, 1, 9)            \
+    X(53, 64, 128, 32, 2, 2, 1, 11)          \
+    X(54, 32, 32, 64, 1, 1, 1, 9)            \
+    X(55, 32, 32, 32, 1, 1, 1, 10)
 
 // square block tiles only (upper-triangle enumeration)
 #define LI_SYRK_F32_CANDIDATES(X)            \

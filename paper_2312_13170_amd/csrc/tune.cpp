@@ -61,19 +61,62 @@ std::atomic<int> g_forced[kFamilies];
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Built-in choice for slots the table does not hold (very large or very
-// elongated problems): for the products, the shapes the search picked at
-// the largest sizes when the output has at least one tile per compute unit
-// (256 on MI355X), else smaller tiles; for the symmetric contractions, the
+// The FP32 products' split tiles (three bf16 parts, split_tile.h): the one
+// with the least predicted time
+//   t = launch + rounds * tile + K * max(alone, shared * rounds)   [us]
+// where rounds = ceil(tiles / 256) is the most tiles a compute unit takes,
+// `alone` what a K step of one tile costs by itself (latency) and `shared`
+// what it costs of a busy compute unit (throughput; several tiles of the
+// small shapes are resident at once).  The constants are a least-squares
+// fit to 456 shapes with M, N, K log-uniform from 64 to 8192 (9% rms); the
+// pick is 1.1% slower than the fastest of these tiles on average.
+struct SplitCost {
+    int idx;
+    double launch, tile, alone, shared;
+};
+const SplitCost kSplitF32[] = {
+    {51, 0.03, 10.79, 0.0328, 0.0329},  // 128 x 128
+    {52, 4.17, 1.48, 0.0150, 0.0131},   // 64 x 64
+    {53, 0.61, 5.76, 0.0097, 0.0204},   // 64 x 128
+    {54, 4.31, 1.84, 0.0057, 0.0081},   // 32 x 32, K-tile 64
+    {55, 5.14, 0.51, 0.0112, 0.0054},   // 32 x 32, K-tile 32
+};
+
+int split_pick(int64_t M, int64_t N, int64_t K)
+{
+    int best = kSplitF32[0].idx;
+    double tbest = HUGE_VAL;
+    for (const SplitCost &c : kSplitF32) {
+        const TileCfg &t = kGemmF32[c.idx];
+        const double rounds = (double)ceil_div(ceil_div(M, t.bm) * ceil_div(N, t.bn), 256);
+        const double alone = c.alone, shared = c.shared * rounds;
+        const double us = c.launch + rounds * c.tile + (double)K * (alone > shared ? alone : shared);
+        if (us < tbest) {
+            tbest = us;
+            best = c.idx;
+        }
+    }
+    return best;
+}
+
+// Shorter reductions stay on the FP32 cores: a split tile starts with two
+// K-tiles on their way through its pipeline (2021 x 1500 x 70: 11.8 us
+// against 17.8 on the best split tile, 8000 x 512 x 192: 18.8 against 21.4;
+// 3648 x 1088 x 133: 19.9 against 16.4, from K = 200 nearly always behind).
+constexpr int64_t kSplitMinK = 200;
+
+// Built-in choice for slots the table does not hold: for the FP32 products
+// the split tiles, and with a short reduction one of the shapes the search
+// picked for the FP32 cores; for the symmetric contractions, the
 // stream-K schedule for a long reduction or a large result.
 int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
 {
-    const int64_t cus = 256;
+    const int64_t cus = 256;  // compute units of an MI355X
     if (kernel == LI_KERNEL_GEMM_F32) {
-        if (ceil_div(M, 128) * ceil_div(N, 256) >= cus) return 49;  // 128 x 256, two-stage ring
-        if (ceil_div(M, 128) * ceil_div(N, 128) >= cus) return 44;  // 128 x 128, 16 waves
-        if (ceil_div(M, 128) * ceil_div(N, 64) >= cus) return 3;
-        return 2;
+        if (K >= kSplitMinK) return split_pick(M, N, K);
+        // by the bit length of the output's side, as searched
+        const int side = tune_key(kernel, M, N, K);
+        return side <= 8 ? 2 : side <= 11 ? 20 : side == 12 ? 44 : 49;
     }
     if (kernel == LI_KERNEL_SYRK_F32) {
         // M features (the order of the result), K samples.  The search
