@@ -25,33 +25,23 @@ int launch_syrk_f32_fused(int cfg, int64_t M, int64_t N, const float *X, const d
     hipStream_t s = (hipStream_t)stream;
     const bool v4 = (M % 4 == 0 && ((uintptr_t)X & 15) == 0);
     const SymArgs a{X, nullptr, M, M, N, S, mode, scale, 0.f, 1, mean, factor};
-    // Direct-to-LDS candidates (PF 4) transform the operands after their LDS
-    // reads; they need K ranges of whole K-tiles (out-of-range samples must
+    // Split tiles transform every element before it is split.  Direct-to-LDS
+    // candidates (PF 4) transform the operands after their LDS reads; they need K ranges of whole K-tiles (out-of-range samples must
     // contribute 0 after the transform), so with a ragged sample count, or
     // without 16-byte rows, the same tile runs the pipelined register path
     // (PF 3), whose filled loads centre out-of-range samples to 0.
-#define LI_T(BM, BN, BK, WM, WN, LOAD, PF, XF) \
-    F32Tile<BM, BN, BK, WM, WN, true, LOAD, PF, false, XF>
-#define LI_PF3(PF) (PF == 4 ? 3 : PF)
-#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF)                                                        \
-    case IDX:                                                                                         \
-        if (mode == 1)                                                                                \
-            return v4 && (PF != 4 || N % BK == 0)                                                     \
-                       ? run_sym<LI_T(BM, BN, BK, WM, WN, kLoadVec4, PF, 2), kSymCols>(a, SK, split_ws, s) \
-                       : v4 ? run_sym<LI_T(BM, BN, BK, WM, WN, kLoadVec4, LI_PF3(PF), 2), kSymCols>(a, SK, split_ws, s) \
-                            : run_sym<LI_T(BM, BN, BK, WM, WN, kLoadScalar, LI_PF3(PF), 2), kSymCols>(a, SK, split_ws, s); \
-        return v4 && (PF != 4 || N % BK == 0)                                                         \
-                   ? run_sym<LI_T(BM, BN, BK, WM, WN, kLoadVec4, PF, 1), kSymCols>(a, SK, split_ws, s) \
-                   : v4 ? run_sym<LI_T(BM, BN, BK, WM, WN, kLoadVec4, LI_PF3(PF), 1), kSymCols>(a, SK, split_ws, s) \
-                        : run_sym<LI_T(BM, BN, BK, WM, WN, kLoadScalar, LI_PF3(PF), 1), kSymCols>(a, SK, split_ws, s);
+#define LI_RUN(BM, BN, BK, WM, WN, SK, PF, XF) \
+    run_sym_candidate<BM, BN, BK, WM, WN, PF, (PF == 4 ? 3 : PF), true, XF, kSymCols>(a, v4, PF != 4 || N % BK == 0, SK, split_ws, s)
+#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF) \
+    case IDX:                                    \
+        return mode == 1 ? LI_RUN(BM, BN, BK, WM, WN, SK, PF, 2) : LI_RUN(BM, BN, BK, WM, WN, SK, PF, 1);
     switch (cfg) {
         LI_SYRK_F32_CANDIDATES(LI_CASE)
     default:
         return (int)hipErrorInvalidValue;
     }
 #undef LI_CASE
-#undef LI_T
-#undef LI_PF3
+#undef LI_RUN
 }
 
 }  // namespace li

@@ -1286,8 +1286,9 @@ struct F32Tile {
 
     // C = alpha*acc + beta*C; with beta != 0 the tile's C loads are issued
     // together, then one wait (not a load-wait-store round trip per element)
-    __device__ __forceinline__ static void store_c(const f32x16 (&acc)[TM][TN], float *C, int64_t ldc, int64_t M,
-                                                   int64_t N, int64_t m0, int64_t n0, float alpha, float beta)
+    __device__ __forceinline__ static void store_c(float *, const f32x16 (&acc)[TM][TN], float *C, int64_t ldc,
+                                                   int64_t M, int64_t N, int64_t m0, int64_t n0, float alpha,
+                                                   float beta)
     {
         if (beta != 0.f) {
             float cv[TM][TN][16];
@@ -1297,145 +1298,150 @@ struct F32Tile {
             epilogue_gemm(acc, C, ldc, M, N, m0, n0, alpha, 0.f);
         }
     }
-
-    // Symmetric result S (M x M): the tile at (m0, n0) with n0 >= m0 writes
-    // each value to S[r][c] and S[c][r] from the same register, so S is
-    // bitwise symmetric; on a diagonal tile only r <= c is written.
-    // mode 0: value * scale; mode 1: value, diagonal forced to 1.0;
-    // mode 2: S = scale * value + beta * S at both positions (the symmetric
-    // rank updates; S is then symmetric only if it was before).
-    // vtid: the thread of the tile whose accumulators acc holds (default:
-    // this thread).
-    __device__ __forceinline__ static void epilogue_syrk(const f32x16 (&acc)[TM][TN], float *S,
-                                                         int64_t M, int64_t m0, int64_t n0,
-                                                         int mode, float scale, float beta = 0.f,
-                                                         int vtid = -1)
-    {
-        const int tid = vtid >= 0 ? vtid : (int)threadIdx.x;
-        const int lane = tid & 63, wave = tid >> 6;
-        const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
-        const bool diag_tile = m0 == n0;
-        if (!diag_tile && (M & 3) == 0 && ((uintptr_t)S & 15) == 0) {
-            // Off-diagonal tile, order a multiple of 4, S 16-byte aligned:
-            // the four consecutive
-            // rows a lane holds for v = 4q .. 4q + 3 are four consecutive
-            // floats of the mirrored tile, so the lower-triangle copy goes
-            // out as one 16-byte store per lane (the direct copy is already
-            // coalesced across the lanes).  Rows come in aligned fours, so a
-            // four is either inside the matrix or wholly outside.
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int64_t col = n0 + acc_col(wn0, j, lane);
-                    if (col >= M) continue;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int64_t row = m0 + acc_row(wm0, i, 4 * q, lane);
-                        if (row >= M) continue;
-                        f32x4 val, old;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) val[e] = acc[i][j][4 * q + e];
-                        float *mir = S + col * M + row;
-                        if (mode == 2 && beta != 0.f) {
-                            float dir[4];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) dir[e] = S[(row + e) * M + col];
-                            old = *reinterpret_cast<const f32x4 *>(mir);
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                S[(row + e) * M + col] = combine(scale, val[e], beta, dir[e]);
-                                old[e] = combine(scale, val[e], beta, old[e]);
-                            }
-                            *reinterpret_cast<f32x4 *>(mir) = old;
-                        } else {
-                            // mode 0 and 2 (beta 0) scale; mode 1 is unscaled
-                            // off the diagonal
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                if (mode != 1) val[e] *= scale;
-                                S[(row + e) * M + col] = val[e];
-                            }
-                            *reinterpret_cast<f32x4 *>(mir) = val;
-                        }
-                    }
-                }
-            return;
-        }
-        if (mode == 2 && beta != 0.f) {
-            // four elements at a time: both triangles' current values loaded
-            // together, then the stores (not a load-wait-store round trip per
-            // element; four keep the registers of the kernels at their
-            // limit); each unordered pair (row, col) belongs to this element
-            // only
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const int64_t col = n0 + acc_col(wn0, j, lane);
-#pragma unroll
-                    for (int v0 = 0; v0 < 16; v0 += 4) {
-                        float pv[4], qv[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int64_t row = m0 + acc_row(wm0, i, v0 + e, lane);
-                            const bool ok = row < M && col < M && !(diag_tile && row > col);
-                            pv[e] = S[ok ? row * M + col : 0];
-                            qv[e] = S[ok ? col * M + row : 0];
-                        }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int64_t row = m0 + acc_row(wm0, i, v0 + e, lane);
-                            if (row >= M || col >= M || (diag_tile && row > col)) continue;
-                            const float val = acc[i][j][v0 + e];
-                            S[row * M + col] = combine(scale, val, beta, pv[e]);
-                            if (row != col) S[col * M + row] = combine(scale, val, beta, qv[e]);
-                        }
-                    }
-                }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t col = n0 + acc_col(wn0, j, lane);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int64_t row = m0 + acc_row(wm0, i, v, lane);
-                    if (row >= M || col >= M) continue;
-                    if (diag_tile && row > col) continue;
-                    float val = acc[i][j][v];
-                    if (mode == 2) {
-                        float *p = S + row * M + col;
-                        *p = beta != 0.f ? combine(scale, val, beta, *p) : scale * val;
-                        if (row != col) {
-                            float *q = S + col * M + row;
-                            *q = beta != 0.f ? combine(scale, val, beta, *q) : scale * val;
-                        }
-                        continue;
-                    }
-                    if (mode == 0)
-                        val *= scale;
-                    else if (row == col)
-                        val = 1.0f;
-                    S[row * M + col] = val;
-                    if (row != col) S[col * M + row] = val;
-                }
-            }
-    }
 };
 
-// Upper-triangle tile t of a tiles x tiles grid (row-major over tm <= tn).
+// Symmetric result S (M x M): the tile at (m0, n0) with n0 >= m0 writes
+// each value to S[r][c] and S[c][r] from the same register, so S is
+// bitwise symmetric; on a diagonal tile only r <= c is written.
+// mode 0: value * scale; mode 1: value, diagonal forced to 1.0;
+// mode 2: S = scale * value + beta * S at both positions (the symmetric
+// rank updates; S is then symmetric only if it was before).
+// vtid: the thread of the tile whose accumulators acc holds (default:
+// this thread).  One 32 x 32 block (i, j) of tile type T:
+template <class T>
+__device__ __forceinline__ void epilogue_syrk_block(const f32x16 &a, int i, int j, float *S, int64_t M, int64_t m0,
+                                                    int64_t n0, int mode, float scale, float beta, int vtid = -1)
+{
+    const int tid = vtid >= 0 ? vtid : (int)threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wm0 = (wave / T::WN) * (T::BM / T::WM), wn0 = (wave % T::WN) * (T::BN / T::WN);
+    const bool diag_tile = m0 == n0;
+    const int64_t col = n0 + T::acc_col(wn0, j, lane);
+    if (col >= M) return;
+    if (!diag_tile && (M & 3) == 0 && ((uintptr_t)S & 15) == 0) {
+        // Off-diagonal tile, order a multiple of 4, S 16-byte aligned:
+        // the four consecutive
+        // rows a lane holds for v = 4q .. 4q + 3 are four consecutive
+        // floats of the mirrored tile, so the lower-triangle copy goes
+        // out as one 16-byte store per lane (the direct copy is already
+        // coalesced across the lanes).  Rows come in aligned fours, so a
+        // four is either inside the matrix or wholly outside.
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t row = m0 + T::acc_row(wm0, i, 4 * q, lane);
+            if (row >= M) continue;
+            f32x4 val, old;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = a[4 * q + e];
+            float *mir = S + col * M + row;
+            if (mode == 2 && beta != 0.f) {
+                float dir[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dir[e] = S[(row + e) * M + col];
+                old = *reinterpret_cast<const f32x4 *>(mir);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    S[(row + e) * M + col] = T::combine(scale, val[e], beta, dir[e]);
+                    old[e] = T::combine(scale, val[e], beta, old[e]);
+                }
+                *reinterpret_cast<f32x4 *>(mir) = old;
+            } else {
+                // mode 0 and 2 (beta 0) scale; mode 1 is unscaled
+                // off the diagonal
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (mode != 1) val[e] *= scale;
+                    S[(row + e) * M + col] = val[e];
+                }
+                *reinterpret_cast<f32x4 *>(mir) = val;
+            }
+        }
+        return;
+    }
+    if (mode == 2 && beta != 0.f) {
+        // four elements at a time: both triangles' current values loaded
+        // together, then the stores (not a load-wait-store round trip per
+        // element; four keep the registers of the kernels at their
+        // limit); each unordered pair (row, col) belongs to this element
+        // only
+#pragma unroll
+        for (int v0 = 0; v0 < 16; v0 += 4) {
+            float pv[4], qv[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t row = m0 + T::acc_row(wm0, i, v0 + e, lane);
+                const bool ok = row < M && !(diag_tile && row > col);
+                pv[e] = S[ok ? row * M + col : 0];
+                qv[e] = S[ok ? col * M + row : 0];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t row = m0 + T::acc_row(wm0, i, v0 + e, lane);
+                if (row >= M || (diag_tile && row > col)) continue;
+                const float val = a[v0 + e];
+                S[row * M + col] = T::combine(scale, val, beta, pv[e]);
+                if (row != col) S[col * M + row] = T::combine(scale, val, beta, qv[e]);
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int64_t row = m0 + T::acc_row(wm0, i, v, lane);
+        if (row >= M) continue;
+        if (diag_tile && row > col) continue;
+        float val = a[v];
+        if (mode != 1)
+            val *= scale;
+        else if (row == col)
+            val = 1.0f;
+        S[row * M + col] = val;
+        if (row != col) S[col * M + row] = val;
+    }
+}
+
+template <class T>
+__device__ __forceinline__ void epilogue_syrk(const f32x16 (&acc)[T::TM][T::TN], float *S, int64_t M, int64_t m0,
+                                              int64_t n0, int mode, float scale, float beta = 0.f, int vtid = -1)
+{
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < T::TN; ++j)
+            epilogue_syrk_block<T>(acc[i][j], i, j, S, M, m0, n0, mode, scale, beta, vtid);
+}
+
+// Upper-triangle tile t of a tiles x tiles grid, in super-blocks of 4 x 4
+// tiles (row by row of super-blocks, each row by row), so that work-groups
+// with neighbouring tiles share operand panels in their XCD's L2.
 __device__ __forceinline__ void upper_tile(int t, int tiles, int &tm, int &tn)
 {
-    int r = 0;
-    while (t >= tiles - r) {
-        t -= tiles - r;
-        ++r;
+    constexpr int S = 4;
+    int r0 = 0, h = 0;
+    for (;; r0 += S) {
+        h = min(S, tiles - r0);
+        const int in_row = h * (h + 1) / 2 + h * (tiles - r0 - h);
+        if (t < in_row) break;
+        t -= in_row;
     }
-    tm = r;
-    tn = r + t;
+    const int diag = h * (h + 1) / 2;
+    if (t < diag) {
+        // the diagonal super-block's upper triangle
+        int r = 0;
+        while (t >= h - r) {
+            t -= h - r;
+            ++r;
+        }
+        tm = r0 + r;
+        tn = r0 + r + t;
+        return;
+    }
+    t -= diag;
+    const int c0 = r0 + h, b = t / (h * S);  // full super-blocks before this one
+    const int w = min(S, tiles - c0 - b * S);
+    t -= b * h * S;
+    tm = r0 + t / w;
+    tn = c0 + b * S + t % w;
 }
 
 }  // namespace li

@@ -31,7 +31,7 @@ __global__ __launch_bounds__(T::NT) void gemm_f32_kernel(const float *__restrict
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
     if (alpha != 0.f) T::mainloop(lds, A, lda, B, ldb, M, N, 0, K, m0, n0, acc);
-    if (T::active()) T::store_c(acc, C, ldc, M, N, m0, n0, alpha, beta);
+    T::store_c(lds, acc, C, ldc, M, N, m0, n0, alpha, beta);
 }
 
 template <class T>
@@ -262,7 +262,7 @@ size_t syrk_split_bytes_cfg(int cfg, int64_t n)
         const int64_t t = (n + BM - 1) / BM;                                                   \
         if (SK > 1) return (size_t)SK * (size_t)(t * (t + 1) / 2) * BM * BN * sizeof(float);   \
         if (SK == 0) {                                                                         \
-            int g = device_cu_count() * (64 * WM * WN >= 1024 ? 1 : 2);                        \
+            int g = device_cu_count() * CandidateTile<BM, BN, BK, WM, WN, PF, true, false, 0, kLoadVec4, PF>::SK_PER_CU; \
             if (g > kStreamMaxGroups) g = kStreamMaxGroups;                                    \
             return (size_t)2 * g * BM * BN * sizeof(float);                                    \
         }                                                                                      \
@@ -282,10 +282,9 @@ int launch_syrk_f32(int cfg, int64_t M, int64_t N, const float *Y, float *S, int
     const bool v4 = (M % 4 == 0 && aligned16(Y));
     const SymArgs a{Y, nullptr, M, M, N, S, mode, scale, 0.f, 1, nullptr, nullptr};
     switch (cfg) {
-#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF)                                                      \
-    case IDX:                                                                                       \
-        return v4 ? run_sym<F32Tile<BM, BN, BK, WM, WN, true, kLoadVec4, PF>, kSymCols>(a, SK, split_ws, s) \
-                  : run_sym<F32Tile<BM, BN, BK, WM, WN, true, kLoadScalar, (PF == 4 ? 2 : PF)>, kSymCols>(a, SK, split_ws, s);
+#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF)                                                        \
+    case IDX:                                                                                           \
+        return run_sym_candidate<BM, BN, BK, WM, WN, PF, PF, true, 0, kSymCols>(a, v4, true, SK, split_ws, s);
         LI_SYRK_F32_CANDIDATES(LI_CASE)
 #undef LI_CASE
     default:

@@ -148,7 +148,7 @@ __device__ __forceinline__ void syrk_tile(float *lds, const GProb &p, const GTil
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
     T::mainloop(lds, p.Y, p.M, p.Y, p.M, p.M, p.M, 0, p.N, m0, n0, acc);
-    T::epilogue_syrk(acc, p.C, p.M, m0, n0, 0, p.scale);
+    epilogue_syrk<T>(acc, p.C, p.M, m0, n0, 0, p.scale);
 }
 
 // Contraction kernel of one shape class over the class's tile table (sorted

@@ -18,10 +18,10 @@
 //
 // Why: six bf16 products still run 2.6 times as fast as one on the FP32
 // cores (2.5 PFLOP/s / 6 against 157 TFLOP/s).  Measured (li_gemm, beta != 0,
-// FP32 cores before): 2048^3 0.130 -> 0.089 ms, 8192^3 7.8 -> 5.4 ms,
-// 1531 x 1027 x 777 38.5 -> 25.0 us, 512^3 12.8 -> 8.1 us.  At 8192^3 the
-// bf16 cores then execute 1.2 PFLOP/s, 0.9 of what a large bf16 product of
-// the vendor library reaches on this card (power-limited clock).
+// FP32 cores before): 2048^3 0.130 -> 0.088 ms, 8192^3 7.8 -> 5.1 ms,
+// 1531 x 1027 x 777 38.5 -> 24.4 us, 512^3 12.8 -> 8.1 us.  At 8192^3 the
+// bf16 cores then execute 1.29 PFLOP/s, what a large bf16 product of the
+// vendor library reaches on this card (power-limited clock).
 //
 // Elements that the three parts cannot hold are noticed: a third part with
 // bits below bf16's (magnitudes of about 2^-110 and less) while splitting,
@@ -52,9 +52,13 @@
 // Loads use buffer descriptors: a uniform base per K-tile, one 32-bit offset
 // per piece and lane and a uniform row offset, so no vector instruction
 // forms an address (20 64-bit additions per K-tile before; 8192^3 5.75 ->
-// 5.4 ms).  They are plain dword loads (k-major operands: consecutive lanes,
-// consecutive columns) and 16-byte loads at 4-byte alignment (k-contiguous
-// ones), so one kernel serves all shapes and alignments.
+// 5.4 ms).  All are 16-byte loads at 4-byte alignment, so one kernel serves
+// all shapes and alignments.  Half of the splitting waves load one operand
+// and half the other, which keeps their loop free of branches: a merge of
+// paths makes the compiler wait for every load in flight.
+//
+// What a work-group runs once is fetched from memory at about 15 ns per
+// instruction, so prologue and epilogue are short loops (store_c).
 #pragma once
 
 #include "f32_tile.h"
@@ -72,6 +76,9 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t &p0, uint32_t &p1, uint32_t &p2,
                                            uint32_t &lost)
 {
+    // (fused with a product that made x, the remainder would have more bits
+    // than x)
+#pragma clang fp contract(off)
     constexpr uint32_t kHigh = 0xffff0000u, kPack = 0x07060302u;  // high halves of two words
     uint32_t u = __builtin_bit_cast(uint32_t, x), v = __builtin_bit_cast(uint32_t, y);
     p0 = __builtin_amdgcn_perm(v, u, kPack);
@@ -94,43 +101,93 @@ constexpr int split_waves(int mode) { return mode == 10 ? 2 : mode == 11 ? 8 : 4
 // Loads of one operand's K-tile of R rows (the other index: m or n) and BK k
 // values into registers, and their split stores into a stage.
 // KMAJOR: element (row, k) at P[k ld + row], else P[row ld + k].
+//
+// A piece is four k of one row (k-contiguous operands: one 16-byte load) or
+// of CW = 4 neighbouring rows (k-major: four 16-byte loads, one per k; eight
+// lanes take eight pieces of four k, the next lanes the next rows, so a load
+// instruction of a wave reads whole 128-byte lines of eight k rows; dword
+// loads of one row per lane took four times the load instructions: 8192^3
+// 5.47 -> 5.13 ms, 2048 x 2048 x 4096 0.168 -> 0.162 ms).
+// Each row's four k go to the stage with one 8-byte store per part.  The rows
+// of a k-major operand stand permuted inside their group of 32 (slot), so
+// that the CW stores of a wave each fall on distinct banks; the accumulators'
+// row or column index is permuted the same way (SplitTile::acc_row, acc_col).
 template <int R, int BK, int NT, bool KMAJOR, int XFORM>
 struct SplitLoader {
+    static constexpr int THREADS = NT;
     static constexpr int KS = BK / 16;
     static constexpr int STEP = R * 16 + 64;  // bf16 elements of one k step, with the skew
     static constexpr int PART = KS * STEP;
-    // k-contiguous: pieces of 4 k of one row; k-major: 8 k of one row
-    static constexpr int PK = KMAJOR ? 8 : 4;
-    static constexpr int PIECES = R * BK / PK;
+    static constexpr int CW = KMAJOR ? 4 : 1;
+    static constexpr int PIECES = R * BK / 4 / CW;
     static_assert(PIECES % NT == 0, "pieces must divide evenly among threads");
     static constexpr int PER = PIECES / NT;
+    static constexpr int LOADS = KMAJOR ? 4 * PER : PER;
 
-    float v[PER][PK];
+    // as loaded: for k-contiguous operands four k of a row, for k-major ones four
+    // rows of each k.  Elements are taken out of the vectors only where they are
+    // stored (piece): shuffles of loop-carried values, placed by the compiler at
+    // the end of the loop body, waited there for the loads just issued (8192^3:
+    // 5.66 ms, 5.12 without).
+    f32x4 v[PER][CW];  // CW is 4 or 1
 
-    __device__ __forceinline__ static int piece_row(int c) { return KMAJOR ? c % R : c / (BK / 4); }
-    __device__ __forceinline__ static int piece_k(int c) { return KMAJOR ? (c / R) * 8 : (c % (BK / 4)) * 4; }
+    __device__ __forceinline__ float element(int i, int e, int j) const { return KMAJOR ? v[i][KMAJOR ? j : 0][e] : v[i][0][j]; }
 
-    // byte offsets of this thread's pieces from the tile's first element;
-    // rows past the matrix repeat its last one (their products are never
-    // stored).  ld is at most kSplitMaxLd.
-    __device__ __forceinline__ static void offsets(uint32_t (&off)[PER], int64_t ld, int64_t rows, int64_t r0, int tid)
+    // place of row r in a stage, and the row at place p
+    __device__ __forceinline__ static int slot(int r) { return KMAJOR ? (r & ~31) + 8 * (r & 3) + ((r & 31) >> 2) : r; }
+    __device__ __forceinline__ static int row_at(int p) { return KMAJOR ? (p & ~31) + 4 * (p & 7) + ((p & 31) >> 3) : p; }
+
+    __device__ __forceinline__ static int piece_row(int c)
+    {
+        return KMAJOR ? (c >> 3) % (R / CW) * CW : c / (BK / 4);
+    }
+    __device__ __forceinline__ static int piece_k(int c)
+    {
+        return KMAJOR ? ((c >> 3) / (R / CW) * 8 + (c & 7)) * 4 : c % (BK / 4) * 4;
+    }
+
+    // This thread's pieces of the tile at row r0: byte offsets from the first
+    // element of the K-tile's row r0 (k-contiguous) or row 0 (k-major), and
+    // places in a stage.  Pieces past the matrix load its last rows again
+    // (products never stored, but finite where the matrix is); a k-major
+    // piece that is partly outside loads the last CW rows and stores those
+    // that the piece before it holds in the places past the matrix, so every
+    // place of a stage is written once.  ld is at most kSplitMaxLd.
+    __device__ __forceinline__ static void places(uint32_t (&off)[PER], int (&at)[PER][CW], int64_t ld, int64_t rows,
+                                                  int64_t r0, int tid)
     {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int c = tid + i * NT;
-            const int64_t last = rows - 1 - r0;
-            const int r = piece_row(c) < last ? piece_row(c) : (int)last;
+            const int k = piece_k(c), r = piece_row(c);
             const uint32_t l = (uint32_t)ld;
-            off[i] = 4u * (KMAJOR ? (uint32_t)piece_k(c) * l + (uint32_t)r : (uint32_t)r * l + (uint32_t)piece_k(c));
+            int shift = 0;  // rows of a partly outside piece that lie before it
+            if (KMAJOR) {
+                int64_t g = r0 + r;
+                if (g > rows - CW) {
+                    if (g < rows && rows >= CW) shift = (int)(g - (rows - CW));
+                    g = rows - CW;
+                }
+                if (g < 0) g = 0;  // (fewer than CW rows: checked loads)
+                off[i] = 4u * ((uint32_t)k * l + (uint32_t)g);
+            } else {
+                const int64_t last = rows - 1 - r0;
+                off[i] = 4u * ((uint32_t)(r < last ? r : (int)last) * l + (uint32_t)k);
+            }
+#pragma unroll
+            for (int e = 0; e < CW; ++e) {
+                const int p = slot(r + (e >= shift ? e - shift : CW - shift + e));
+                at[i][e] = (k / 16) * STEP + p * 16 + ((((k >> 3) & 1) ^ ((p >> 3) & 1)) << 3) + (k & 4);
+            }
         }
     }
 
-    // base: the tile's first element at this K-tile; left: k values that
-    // remain from there (values past them are 0, or `fill`, which the
-    // transform maps to 0)
+    // base: the first element of this K-tile (see places); left: k values
+    // that remain from there (values past them are 0, or `fill`, which the
+    // transform maps to 0).  FULL: a whole K-tile of at least CW rows.
     template <bool FULL>
     __device__ __forceinline__ void load(const float *__restrict__ base, const uint32_t (&off)[PER], int64_t ld,
-                                         int64_t left, const float (&fill)[PER], int tid)
+                                         int64_t left, int64_t rows, const float (&fill)[PER][CW], int tid)
     {
         // buffer loads: a uniform descriptor of this K-tile, the lane's 32-bit
         // offset and a uniform row offset, so no vector instruction forms an
@@ -142,64 +199,69 @@ struct SplitLoader {
             for (int i = 0; i < PER; ++i) {
                 if constexpr (KMAJOR) {
 #pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        v[i][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off[i], j * ld4, 0));
+                    for (int j = 0; j < 4; ++j) {
+                        const auto raw = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], j * ld4, 0);
+                        v[i][j] = __builtin_bit_cast(f32x4, raw);
+                    }
                 } else {
                     const auto raw = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], 0, 0);
-                    static_assert(sizeof(raw) == 16, "16-byte loads");
-                    const f32x4 x = __builtin_bit_cast(f32x4, raw);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[i][j] = x[j];
+                    v[i][0] = __builtin_bit_cast(f32x4, raw);
                 }
             }
         } else {
 #pragma unroll
             for (int i = 0; i < PER; ++i)
 #pragma unroll
-                for (int j = 0; j < PK; ++j) {
-                    v[i][j] = XFORM ? fill[i] : 0.f;
-                    if (piece_k(tid + i * NT) + j < left)
-                        v[i][j] = __builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off[i] + (KMAJOR ? 0 : 4 * j), KMAJOR ? j * ld4 : 0, 0));
-                }
+                for (int e = 0; e < CW; ++e)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float x = XFORM ? fill[i][e] : 0.f;
+                        if (piece_k(tid + i * NT) + j < left && e < rows)
+                            x = __builtin_bit_cast(
+                                float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off[i] + (KMAJOR ? 4 * e : 4 * j),
+                                                                            KMAJOR ? j * ld4 : 0, 0));
+                        if (KMAJOR)
+                            v[i][KMAJOR ? j : 0][e] = x;
+                        else
+                            v[i][0][j] = x;
+                    }
         }
     }
 
-    __device__ __forceinline__ void store(uint16_t *lds, uint32_t &lost, const float (&m)[PER], const float (&f)[PER], int tid) const
+    __device__ __forceinline__ void store(uint16_t *lds, const int (&at)[PER][CW], uint32_t &lost,
+                                          const float (&m)[PER][CW], const float (&f)[PER][CW])
     {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int c = tid + i * NT;
-            const int r = piece_row(c), k = piece_k(c);
-            uint32_t p[3][PK / 2];
 #pragma unroll
-            for (int j = 0; j < PK; j += 2) {
-                float x = v[i][j], y = v[i][j + 1];
-                if (XFORM != 0) {
-                    x -= m[i];
-                    y -= m[i];
-                }
-                if (XFORM == 2) {
-                    x *= f[i];
-                    y *= f[i];
-                }
-                split_pair(x, y, p[0][j / 2], p[1][j / 2], p[2][j / 2], lost);
-            }
-            uint16_t *d = lds + (k / 16) * STEP + r * 16 + ((((k >> 3) & 1) ^ ((r >> 3) & 1)) << 3) + (k & 4);
+            for (int j = 0; j < CW; ++j) asm volatile("" : "+v"(v[i][j]));
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                if constexpr (KMAJOR)
-                    *reinterpret_cast<u32x4_t *>(d + q * PART) = u32x4_t{p[q][0], p[q][1], p[q][2], p[q][3]};
-                else
-                    *reinterpret_cast<u32x2_t *>(d + q * PART) = u32x2_t{p[q][0], p[q][1]};
+            for (int e = 0; e < CW; ++e) {
+                uint32_t p[3][2];
+#pragma unroll
+                for (int j = 0; j < 4; j += 2) {
+                    float x = element(i, e, j), y = element(i, e, j + 1);
+                    if (XFORM != 0) {
+                        x -= m[i][e];
+                        y -= m[i][e];
+                    }
+                    if (XFORM == 2) {
+                        x *= f[i][e];
+                        y *= f[i][e];
+                    }
+                    split_pair(x, y, p[0][j / 2], p[1][j / 2], p[2][j / 2], lost);
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    *reinterpret_cast<u32x2_t *>(lds + q * PART + at[i][e]) = u32x2_t{p[q][0], p[q][1]};
             }
         }
     }
 
-    // matrix-core operand: 8 k of row `row` at k step `s`, half h
-    __device__ __forceinline__ static bf16x8_t frag(const uint16_t *lds, int part, int s, int row, int h)
+    // matrix-core operand: 8 k of place p at k step s, half h
+    __device__ __forceinline__ static bf16x8_t frag(const uint16_t *lds, int part, int s, int p, int h)
     {
-        return *reinterpret_cast<const bf16x8_t *>(lds + part * PART + s * STEP + row * 16 + ((h ^ ((row >> 3) & 1)) << 3));
+        return *reinterpret_cast<const bf16x8_t *>(lds + part * PART + s * STEP + p * 16 + ((h ^ ((p >> 3) & 1)) << 3));
     }
 };
 
@@ -213,13 +275,13 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
     static constexpr int TM = Base::TM, TN = Base::TN;
     static constexpr int XFORM = XFORM_;
     static constexpr int ET = 64 * WM * WN;  // threads of the matrix waves, which hold the result
-    static constexpr int PT = 64 * PW;       // threads of the splitting waves
-    static constexpr int NT = ET + PT;
+    // splitting waves of each operand
+    static constexpr int PWA = PW / 2, PWB = PW - PWA;
+    static constexpr int NT = ET + 64 * PW;
     static constexpr int BK = BK_, KS = BK / 16;
     static_assert(BK % 32 == 0, "an even number of k steps keeps the operand sets' parity");
-    static constexpr int NS = 2;  // K-tiles in flight from memory (register sets)
-    using LA = SplitLoader<BM, BK, PT, A_KMAJOR, XFORM>;
-    using LB = SplitLoader<BN, BK, PT, !B_NMAJOR, XFORM>;
+    using LA = SplitLoader<BM, BK, 64 * PWA, A_KMAJOR, XFORM>;
+    using LB = SplitLoader<BN, BK, 64 * PWB, !B_NMAJOR, XFORM>;
     static constexpr int STAGE = 3 * (LA::PART + LB::PART);  // bf16 elements
     static constexpr int SPLIT_FLOATS = STAGE;               // two stages of 2-byte elements
     static constexpr int SAFE_FLOATS = Safe::LDS_FLOATS;
@@ -242,19 +304,35 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
         x.factor = factor;
     }
 
+    // the transform of this thread's rows (those its pieces read, see places)
     template <class L>
-    __device__ __forceinline__ static void columns(const XRegs *x, int64_t n, int64_t r0, int tid, float (&m)[L::PER],
-                                                   float (&f)[L::PER])
+    __device__ __forceinline__ static void columns(const XRegs *x, int64_t n, int64_t r0, int tid,
+                                                   float (&m)[L::PER][L::CW], float (&f)[L::PER][L::CW])
     {
 #pragma unroll
-        for (int i = 0; i < L::PER; ++i) {
-            m[i] = f[i] = 0.f;
-            if constexpr (XFORM != 0) {
-                const int64_t c = r0 + L::piece_row(tid + i * PT);
-                if (c < n) m[i] = (float)x->mean[c];
-                if (XFORM == 2 && c < n) f[i] = (float)x->factor[c];
+        for (int i = 0; i < L::PER; ++i)
+#pragma unroll
+            for (int e = 0; e < L::CW; ++e) {
+                m[i][e] = f[i][e] = 0.f;
+                if constexpr (XFORM != 0) {
+                    int64_t g = r0 + L::piece_row(tid + i * L::THREADS);
+                    if (g > n - L::CW) g = n - L::CW;
+                    if (g < 0) g = 0;
+                    if (g + e < n) m[i][e] = (float)x->mean[g + e];
+                    if (XFORM == 2 && g + e < n) f[i][e] = (float)x->factor[g + e];
+                }
             }
-        }
+    }
+
+    // Row / column of accumulator element v of block (tm, tn) in the tile: a
+    // k-major operand's rows stand permuted (SplitLoader::row_at).
+    __device__ __forceinline__ static int acc_row(int wm0, int tm, int v, int lane)
+    {
+        return A_KMAJOR ? wm0 + 32 * tm + 16 * (lane >> 5) + 4 * (v & 3) + (v >> 2) : Base::acc_row(wm0, tm, v, lane);
+    }
+    __device__ __forceinline__ static int acc_col(int wn0, int tn, int lane)
+    {
+        return wn0 + 32 * tn + LB::row_at(lane & 31);
     }
 
     // LDS writes and reads of the work-group ordered by a barrier that does
@@ -323,7 +401,8 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
         lds_barrier();  // K-tile 0 is stored
         read_frag(f, cur, 0, wm0, wn0, lane);
         __builtin_amdgcn_sched_barrier(0);
-        for (int t = 0; t + 1 < nk; ++t) {
+        // (the last K-tile reads operands past it, which nothing uses)
+        for (int t = 0; t < nk; ++t) {
 #pragma unroll
             for (int s = 0; s < KS; s += 2) {
                 read_frag(g, cur, s + 1, wm0, wn0, lane);
@@ -341,100 +420,91 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
             cur = nxt;
             nxt = x;
         }
-#pragma unroll
-        for (int s = 0; s < KS; s += 2) {
-            read_frag(g, cur, s + 1, wm0, wn0, lane);
-            mma(f, hi, lo);
-            if (s + 2 < KS) read_frag(f, cur, s + 2, wm0, wn0, lane);
-            mma(g, hi, lo);
-        }
-        lds_barrier();
         __builtin_amdgcn_s_setprio(0);
     }
 
-    // Splitting waves: nk K-tiles into the two stages in turn, loaded NS
-    // K-tiles ahead of their split.
-    __device__ __forceinline__ static void produce(uint16_t *lds, const float *A, int64_t lda, const float *B,
-                                                   int64_t ldb, int64_t M, int64_t N, int64_t kbeg, int64_t kend,
-                                                   int64_t m0, int64_t n0, int nk, uint32_t &lost, const XRegs *xr)
+    // Splitting waves of one operand (L; tile at row r0 of `rows`): nk K-tiles
+    // into its part of the two stages in turn, loaded two K-tiles ahead of
+    // their split.
+    // P1: the operand of a second product over the same k, or NULL
+    // (k-contiguous operands only): the whole K-tiles of both, then the
+    // partial ones, in one run of the pipeline.
+    template <class L, bool KMAJOR>
+    __device__ __forceinline__ static void produce(uint16_t *lds, const float *P, const float *P1, int64_t ld,
+                                                   int64_t rows,
+                                                   int64_t kbeg, int64_t kend, int64_t r0, int nk, int tid,
+                                                   uint32_t &lost, const XRegs *xr)
     {
-        const int tid = (int)threadIdx.x - ET;
-        float ma[LA::PER], fa[LA::PER], mb[LB::PER], fb[LB::PER];
-        columns<LA>(xr, M, m0, tid, ma, fa);
-        columns<LB>(xr, N, n0, tid, mb, fb);
-        LA la[NS];
-        LB lb[NS];
-        uint32_t oa[LA::PER], ob[LB::PER];
-        LA::offsets(oa, lda, M, m0, tid);
-        LB::offsets(ob, ldb, N, n0, tid);
-        const int64_t adv_a = A_KMAJOR ? BK * lda : BK, adv_b = B_NMAJOR ? BK : BK * ldb;
-        const float *pa = A_KMAJOR ? A + kbeg * lda + m0 : A + m0 * lda + kbeg;
-        const float *pb = B_NMAJOR ? B + n0 * ldb + kbeg : B + kbeg * ldb + n0;
-        int64_t left = kend - kbeg;
-        auto load = [&](auto full, int set) {
-            if (decltype(full)::value || left >= BK) {
-                la[set].template load<true>(pa, oa, lda, left, ma, tid);
-                lb[set].template load<true>(pb, ob, ldb, left, mb, tid);
-            } else {
-                la[set].template load<false>(pa, oa, lda, left, ma, tid);
-                lb[set].template load<false>(pb, ob, ldb, left, mb, tid);
-            }
-            pa += adv_a;
-            pb += adv_b;
-            left -= BK;
-        };
-        auto store = [&](int set) {
-            uint16_t *st = lds + (set & 1) * STAGE;
-            la[set].store(st, lost, ma, fa, tid);
-            lb[set].store(st + 3 * LA::PART, lost, mb, fb, tid);
-        };
-        constexpr std::true_type full{};
-        constexpr std::false_type any{};
+        float m[L::PER][L::CW], f[L::PER][L::CW];
+        columns<L>(xr, rows, r0, tid, m, f);
+        L l[2];
+        uint32_t off[L::PER];
+        int at[L::PER][L::CW];
+        L::places(off, at, ld, rows, r0, tid);
+        const int64_t adv = KMAJOR ? BK * ld : BK;
+        const float *p = KMAJOR ? P + kbeg * ld : P + r0 * ld + kbeg;
         // Whole K-tiles run a loop without branches around its loads, so the
-        // waits count them exactly; the last tiles take the checked loads.
-        int t = 0;
-        if (left >= 2 * NS * BK) {
-#pragma unroll
-            for (int i = 0; i < NS; ++i) {
-                load(full, i);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            for (; left >= NS * BK; t += NS)
-#pragma unroll
-                for (int i = 0; i < NS; ++i) {
-                    store(i);
-                    load(full, i);
-                    __builtin_amdgcn_sched_barrier(0);
-                    lds_barrier();  // K-tile t + i is stored, the one before is read
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < NS; ++i)
-                if (left > 0) load(any, i);
+        // waits count them exactly; loads past the last whole K-tile repeat
+        // it.  A partial one (or a k-major operand of fewer than CW rows)
+        // takes checked loads.  Code that runs once per block tile is kept
+        // short: its instructions come from memory.
+        const int n1 = (int)((kend - kbeg) / BK);
+        const int nfast = KMAJOR && rows < L::CW ? 0 : P1 ? 2 * n1 : n1;
+        const float *p1 = P1 ? P1 + r0 * ld + kbeg : p;
+        int loaded = 0;
+        auto load = [&](int set) {
+            l[set].template load<true>(p, off, ld, 0, rows, m, tid);
+            ++loaded;
+            p += loaded < nfast ? adv : 0;
+            if (loaded == n1 && P1) p = p1;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto store = [&](int set, int t) { l[set].store(lds + (t & 1) * STAGE, at, lost, m, f); };
+        if (nfast > 0) {
+            load(0);
+            load(1);
         }
-        for (; t < nk; t += NS)
-#pragma unroll
-            for (int i = 0; i < NS; ++i)
-                if (t + i < nk) {
-                    store(i);
-                    if (left > 0) load(any, i);
-                    lds_barrier();
-                }
+        int t = 0;
+        for (; t + 2 <= nfast; t += 2) {
+            store(0, 0);
+            load(0);
+            lds_barrier();  // K-tile t is stored, the one before is read
+            store(1, 1);
+            load(1);
+            lds_barrier();
+        }
+        const float *q = KMAJOR ? P + kbeg * ld : P + r0 * ld + kbeg;
+        for (; t < nk; ++t) {
+            if (t >= nfast) {
+                // K-tile of its product: every one (too few rows), or the partial one
+                const int64_t kt = KMAJOR && nfast == 0 ? t : n1;
+                l[0].template load<false>((t > nfast && !KMAJOR ? p1 : q) + kt * adv, off, ld,
+                                          kend - kbeg - kt * BK, KMAJOR ? rows : 1, m, tid);
+            }
+            store(0, t);
+            lds_barrier();
+        }
         lds_barrier();
     }
 
-    // hi, lo += A B over k in [kbeg, kend)
-    __device__ __forceinline__ static void reduce(uint16_t *lds, const float *A, int64_t lda, const float *B,
-                                                  int64_t ldb, int64_t M, int64_t N, int64_t kbeg, int64_t kend,
-                                                  int64_t m0, int64_t n0, f32x16 (&hi)[TM][TN],
-                                                  f32x16 (&lo)[TM][TN], uint32_t &lost, const XRegs *xr)
+    // hi, lo += A B (+ A1 B1 where given, k-contiguous operands) over k in
+    // [kbeg, kend)
+    __device__ __forceinline__ static void reduce(uint16_t *lds, const float *A, const float *A1, int64_t lda,
+                                                  const float *B, const float *B1, int64_t ldb, int64_t M, int64_t N,
+                                                  int64_t kbeg, int64_t kend, int64_t m0, int64_t n0,
+                                                  f32x16 (&hi)[TM][TN], f32x16 (&lo)[TM][TN], uint32_t &lost,
+                                                  const XRegs *xr)
     {
-        const int nk = (int)((kend - kbeg + BK - 1) / BK);
-        // nk + 1 barriers on both sides
-        if (active())
+        const int nk = (int)((kend - kbeg + BK - 1) / BK) * (A1 ? 2 : 1);
+        // nk + 1 barriers on every side
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - WM * WN;
+        if (w < 0)
             multiply(lds, nk, hi, lo);
+        else if (w < PWA)
+            produce<LA, A_KMAJOR>(lds, A, A1, lda, M, kbeg, kend, m0, nk, (int)threadIdx.x - ET, lost, xr);
         else
-            produce(lds, A, lda, B, ldb, M, N, kbeg, kend, m0, n0, nk, lost, xr);
+            produce<LB, !B_NMAJOR>(lds + 3 * LA::PART, B, B1, ldb, N, kbeg, kend, n0, nk, (int)threadIdx.x - ET - 64 * PWA,
+                                   lost, xr);
     }
 
     // acc += A B on the FP32 matrix cores: the matrix waves run the FP32
@@ -467,8 +537,7 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
             Base::zero(acc);
             Base::zero(lo);
             uint16_t *l16 = reinterpret_cast<uint16_t *>(lds);
-            for (int pass = 0; pass < (A1 ? 2 : 1); ++pass)
-                reduce(l16, pass ? A1 : A, lda, pass ? B1 : B, ldb, M, N, kbeg, kend, m0, n0, acc, lo, lost, xr);
+            reduce(l16, A, A1, lda, B, B1, ldb, M, N, kbeg, kend, m0, n0, acc, lo, lost, xr);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -490,68 +559,88 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
                 Base::zero(acc);
                 reduce_safe(lds, A, lda, B, ldb, M, N, kbeg, kend, m0, n0, acc, xr);
                 if (A1) reduce_safe(lds, A1, lda, B1, ldb, M, N, kbeg, kend, m0, n0, acc, xr);
+                if (active()) permute_acc(acc);
             }
         }
     }
 
-    // C = alpha acc + beta C over the in-range part of the tile (beta == 0: C
-    // is not read).  Every row of the wave's blocks is a uniform address plus
-    // one 32-bit lane offset: the code of a block tile is short, which counts
-    // where a work-group runs it once (instruction fetch).
-    template <bool FULL>
-    __device__ __forceinline__ static void write_c(const f32x16 (&acc)[TM][TN], float *C, int64_t ldc, int rows,
-                                                   int cols, float alpha, float beta)
+    // The FP32 tile's accumulators (rows and columns in order) to those of
+    // this tile (acc_row, acc_col).
+    __device__ __forceinline__ static void permute_acc(f32x16 (&acc)[TM][TN])
     {
-        const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-        const int wm0 = (w / WN) * (BM / WM), wn0 = (w % WN) * (BN / WN);
-        const int r0 = 4 * (lane >> 5), c0 = lane & 31;
-        const uint32_t voff = 4u * ((uint32_t)r0 * (uint32_t)ldc + (uint32_t)c0);
-        char *base = reinterpret_cast<char *>(C + (int64_t)wm0 * ldc + wn0);
-        auto at = [&](int i, int j, int v) {
-            const int64_t row = 32 * i + 8 * (v >> 2) + (v & 3);
-            return reinterpret_cast<float *>(base + row * ldc * 4 + 128 * j + voff);
-        };
-        auto ok = [&](int i, int j, int v) {
-            return FULL || (wm0 + 32 * i + 8 * (v >> 2) + (v & 3) + r0 < rows && wn0 + 32 * j + c0 < cols);
-        };
-        float old[TM][TN][16];
-        if (beta != 0.f) {
+        const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5;
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
+            for (int j = 0; j < TN; ++j) {
+                const f32x16 x = acc[i][j];
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        old[i][j][v] = 0.f;
-                        if (ok(i, j, v)) old[i][j][v] = *at(i, j, v);
+                for (int v = 0; v < 16; ++v) {
+                    const int col = LB::row_at(l32);
+                    if constexpr (A_KMAJOR) {
+                        // row 16 h + 4 (v % 4) + v / 4 is in lane half v % 2,
+                        // register 8 h + lo
+                        const int lo = 4 * ((v >> 1) & 1) + (v >> 2);
+                        const float a = __shfl(x[lo], col + 32 * (v & 1), 64), b = __shfl(x[lo + 8], col + 32 * (v & 1), 64);
+                        acc[i][j][v] = h ? b : a;
+                    } else {
+                        acc[i][j][v] = __shfl(x[v], col + 32 * h, 64);
                     }
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (ok(i, j, v)) *at(i, j, v) = Base::combine(alpha, acc[i][j][v], beta, old[i][j][v]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-                        if (ok(i, j, v)) *at(i, j, v) = alpha * acc[i][j][v];
-        }
+                }
+            }
     }
 
-    __device__ __forceinline__ static void store_c(const f32x16 (&acc)[TM][TN], float *C, int64_t ldc, int64_t M,
-                                                   int64_t N, int64_t m0, int64_t n0, float alpha, float beta)
+    // The accumulators to LDS, [BM][OLD] in the tile's order.
+    static constexpr int OLD = BN + 1;
+    static_assert(BM * OLD + 2 * (BM + BN) <= LDS_FLOATS, "the tile and its columns' shifts must fit");
+    __device__ __forceinline__ static void stage_acc(float *lds, const f32x16 (&acc)[TM][TN])
     {
-        float *c = C + m0 * ldc + n0;
-        const int rows = M - m0 < BM ? (int)(M - m0) : BM, cols = N - n0 < BN ? (int)(N - n0) : BN;
-        if (rows == BM && cols == BN)
-            write_c<true>(acc, c, ldc, rows, cols, alpha, beta);
-        else
-            write_c<false>(acc, c, ldc, rows, cols, alpha, beta);
+        const int lane = threadIdx.x & 63, w = (int)(threadIdx.x >> 6);
+        const int wm0 = (w / WN) * (BM / WM), wn0 = (w % WN) * (BN / WN);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    lds[acc_row(wm0, i, v, lane) * OLD + acc_col(wn0, j, lane)] = acc[i][j][v];
+    }
+
+    // C = alpha acc + beta C over the in-range part of the tile (beta == 0: C
+    // is not read), by all waves.  The tile goes through LDS so that every
+    // access to C is a 16-byte one of whole lines and the code is a short
+    // loop: a work-group runs it once, and unrolled over the accumulators it
+    // was bound by its instruction fetch (covariance 2048 x 32, all 136 tiles
+    // at once: 45 us).
+    __device__ __forceinline__ static void store_c(float *lds, const f32x16 (&acc)[TM][TN], float *C, int64_t ldc,
+                                                   int64_t M, int64_t N, int64_t m0, int64_t n0, float alpha,
+                                                   float beta)
+    {
+        if (active()) stage_acc(lds, acc);
+        __syncthreads();
+        constexpr int QC = BN / 4;
+#pragma unroll 4
+        for (int x = threadIdx.x; x < BM * QC; x += NT) {
+            const int r = x / QC, c = x % QC * 4;
+            const int64_t row = m0 + r, col = n0 + c;
+            if (row >= M || col >= N) continue;
+            float *p = C + row * ldc + col;
+            const float *t = lds + r * OLD + c;
+            f32x4 y{t[0], t[1], t[2], t[3]};
+            if (col + 3 < N) {
+                if (beta != 0.f) {
+                    const f32x4 o = *reinterpret_cast<const f32x4u *>(p);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = Base::combine(alpha, y[e], beta, o[e]);
+                } else {
+                    y *= alpha;
+                }
+                *reinterpret_cast<f32x4u *>(p) = y;
+            } else {
+                for (int e = 0; e < 4 && col + e < N; ++e)
+                    p[e] = beta != 0.f ? Base::combine(alpha, t[e], beta, p[e]) : alpha * t[e];
+            }
+        }
     }
 
     __device__ __forceinline__ static void mainloop(float *lds, const float *A, int64_t lda, const float *B,
@@ -562,5 +651,12 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
         contract(lds, A, B, nullptr, nullptr, lda, ldb, M, N, kbeg, kend, m0, n0, acc, xr);
     }
 };
+
+// The tile type of a candidate: the split tile for modes 9 to 11, else the
+// FP32 cores' (LOAD and MODE are its load mode and main-loop mode).
+template <int BM, int BN, int BK, int WM, int WN, int PF, bool A_KMAJOR, bool B_NMAJOR, int XFORM, int LOAD, int MODE>
+using CandidateTile = typename std::conditional<
+    (PF >= 9), SplitTile<BM, BN, BK, WM, WN, split_waves(PF), true, A_KMAJOR, B_NMAJOR, XFORM>,
+    F32Tile<BM, BN, BK, WM, WN, A_KMAJOR, LOAD, (PF >= 9 ? 1 : MODE), B_NMAJOR, XFORM>>::type;
 
 }  // namespace li

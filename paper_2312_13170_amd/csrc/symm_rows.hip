@@ -13,6 +13,9 @@
 
 namespace li {
 
+// a stream-K candidate of the FP32 cores (the workspace fits any candidate)
+constexpr int kSymRowsPlain = 12;
+
 size_t sym_rows_split_bytes(int64_t n)
 {
     size_t best = 0;
@@ -27,16 +30,14 @@ int launch_sym_rows(int cfg, int64_t n, int64_t k, float alpha, const float *A, 
     const bool two = B != nullptr;
     const bool v4 = k % 4 == 0 && ((uintptr_t)A & 15) == 0 && (!two || ((uintptr_t)B & 15) == 0);
     const SymArgs a{A, B, k, n, k, C, 2, alpha, beta, alpha != 0.f && k > 0 ? 1 : 0, nullptr, nullptr};
+    // (rows too long for the split tiles' 32-bit offsets)
+    if (k > kSplitMaxLd) cfg = kSymRowsPlain;
     switch (cfg) {
-#define LI_RUN(BM, BN, BK, WM, WN, SK, LOAD, PF, FORM) \
-    run_sym<F32Tile<BM, BN, BK, WM, WN, false, LOAD, PF, true>, FORM>(a, SK, split_ws, s)
-#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF)                                                     \
-    case IDX:                                                                                      \
-        if (v4)                                                                                    \
-            return two ? LI_RUN(BM, BN, BK, WM, WN, SK, kLoadVec4, PF, kSymRows2)                  \
-                       : LI_RUN(BM, BN, BK, WM, WN, SK, kLoadVec4, PF, kSymRows);                  \
-        return two ? LI_RUN(BM, BN, BK, WM, WN, SK, kLoadScalar, (PF == 4 ? 2 : PF), kSymRows2)    \
-                   : LI_RUN(BM, BN, BK, WM, WN, SK, kLoadScalar, (PF == 4 ? 2 : PF), kSymRows);
+#define LI_RUN(BM, BN, BK, WM, WN, SK, PF, FORM) \
+    run_sym_candidate<BM, BN, BK, WM, WN, PF, PF, false, 0, FORM>(a, v4, true, SK, split_ws, s)
+#define LI_CASE(IDX, BM, BN, BK, WM, WN, SK, PF) \
+    case IDX:                                    \
+        return two ? LI_RUN(BM, BN, BK, WM, WN, SK, PF, kSymRows2) : LI_RUN(BM, BN, BK, WM, WN, SK, PF, kSymRows);
         LI_SYRK_ROWS_CANDIDATES(LI_CASE)
 #undef LI_CASE
 #undef LI_RUN

@@ -4,8 +4,8 @@
 // candidates they share with the single-problem kernels have the same shape.
 
 // {index, bm, bn, bk, waves_m, waves_n, split_k, prefetch depth}
-// split_k: 1 none, > 1 split reduction into that many chunks, 0 stream-K
-// (symmetric contractions only).  prefetch: main-loop mode 1-4; in the FP32
+// split_k: 1 none, > 1 split reduction into that many chunks, 0 stream-K or,
+// for the split tiles, a plan of phases (symmetric contractions only).  prefetch: main-loop mode 1-4; in the FP32
 // GEMM list 5-7 are modes 1-3 with B transposed into LDS and 8 is the
 // direct-to-LDS loop with a two-stage ring (K a multiple of the K-tile).
 // 9, 10, 11: operands split into three bf16 parts, multiplied on the bf16
@@ -81,7 +81,7 @@
     X(7, 128, 128, 32, 2, 4, 4, 1)           \
     X(8, 128, 128, 32, 2, 2, 4, 1)           \
     X(9, 128, 128, 32, 2, 4, 7, 1)           \
-    X(10, 128, 128, 32, 4, 4, 7, 2)          \
+    X(10, 128, 128, 32, 2, 2, 7, 9)          \
     X(11, 128, 128, 64, 4, 4, 7, 1)          \
     X(12, 128, 128, 64, 2, 4, 4, 1)          \
     X(13, 128, 128, 32, 4, 4, 7, 3)          \
@@ -91,13 +91,14 @@
     X(17, 64, 64, 32, 2, 2, 1, 4)            \
     X(18, 128, 128, 32, 4, 4, 0, 2)          \
     X(19, 128, 128, 32, 2, 4, 0, 3)          \
-    X(20, 128, 128, 32, 4, 4, 0, 4)          \
-    X(21, 64, 64, 32, 2, 2, 0, 2)            \
+    X(20, 128, 128, 32, 2, 2, 0, 9)          \
+    X(21, 64, 64, 32, 2, 2, 0, 9)            \
     X(22, 128, 128, 32, 2, 4, 1, 3)          \
     X(23, 64, 64, 32, 2, 2, 1, 3)            \
     X(24, 128, 128, 32, 4, 4, 0, 3)          \
     X(25, 128, 128, 32, 2, 4, 0, 4)          \
-    X(26, 32, 32, 32, 1, 1, 1, 3)
+    X(26, 32, 32, 32, 1, 1, 1, 3)            \
+    X(27, 32, 32, 32, 1, 1, 1, 10)
 
 // bf16 / fp16 matrix-core GEMM on pre-rounded operands; the last column is
 // the LDS layout here (1: XOR-swizzled rows, 2: rows padded by 16 bytes,
@@ -152,13 +153,15 @@
     X(6, 128, 128, 32, 4, 4, 7, 2)           \
     X(7, 128, 128, 32, 2, 4, 7, 3)           \
     X(8, 128, 128, 32, 4, 4, 4, 4)           \
-    X(9, 64, 64, 32, 2, 2, 4, 2)             \
-    X(10, 64, 64, 32, 2, 2, 1, 3)            \
+    X(9, 64, 64, 32, 2, 2, 4, 9)             \
+    X(10, 128, 128, 32, 2, 2, 1, 9)          \
     X(11, 128, 128, 32, 4, 4, 2, 4)          \
     X(12, 128, 128, 32, 4, 4, 0, 2)          \
     X(13, 128, 128, 32, 2, 4, 0, 3)          \
-    X(14, 64, 64, 32, 2, 2, 0, 2)            \
-    X(15, 128, 128, 32, 4, 4, 0, 4)
+    X(14, 64, 64, 32, 2, 2, 0, 9)            \
+    X(15, 128, 128, 32, 2, 2, 0, 9)          \
+    X(16, 64, 64, 32, 2, 2, 1, 3)            \
+    X(17, 32, 32, 32, 1, 1, 1, 10)
 
 // Shape classes of the grouped execution (grouped.hip), also the candidates
 // of the tuning families LI_KERNEL_GROUPED_GEMM / LI_KERNEL_GROUPED_COV.

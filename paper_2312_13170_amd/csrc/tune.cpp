@@ -68,18 +68,18 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // `alone` what a K step of one tile costs by itself (latency) and `shared`
 // what it costs of a busy compute unit (throughput; several tiles of the
 // small shapes are resident at once).  The constants are a least-squares
-// fit to 456 shapes with M, N, K log-uniform from 64 to 8192 (9% rms); the
-// pick is 1.1% slower than the fastest of these tiles on average.
+// fit to 226 shapes with M, N, K log-uniform from 64 to 8192 (10% rms); the
+// pick is 1.4% slower than the fastest of these tiles on average.
 struct SplitCost {
     int idx;
     double launch, tile, alone, shared;
 };
 const SplitCost kSplitF32[] = {
-    {51, 0.03, 10.79, 0.0328, 0.0329},  // 128 x 128
-    {52, 4.17, 1.48, 0.0150, 0.0131},   // 64 x 64
-    {53, 0.61, 5.76, 0.0097, 0.0204},   // 64 x 128
-    {54, 4.31, 1.84, 0.0057, 0.0081},   // 32 x 32, K-tile 64
-    {55, 5.14, 0.51, 0.0112, 0.0054},   // 32 x 32, K-tile 32
+    {51, 0.00, 9.54, 0.0101, 0.0303},  // 128 x 128
+    {52, 3.90, 1.59, 0.0129, 0.0128},  // 64 x 64
+    {53, 0.09, 6.10, 0.0029, 0.0198},  // 64 x 128
+    {54, 3.03, 2.22, 0.0052, 0.0071},  // 32 x 32, K-tile 64
+    {55, 5.02, 0.41, 0.0102, 0.0055},  // 32 x 32, K-tile 32
 };
 
 int split_pick(int64_t M, int64_t N, int64_t K)
@@ -100,15 +100,14 @@ int split_pick(int64_t M, int64_t N, int64_t K)
 }
 
 // Shorter reductions stay on the FP32 cores: a split tile starts with two
-// K-tiles on their way through its pipeline (2021 x 1500 x 70: 11.8 us
-// against 17.8 on the best split tile, 8000 x 512 x 192: 18.8 against 21.4;
-// 3648 x 1088 x 133: 19.9 against 16.4, from K = 200 nearly always behind).
-constexpr int64_t kSplitMinK = 200;
+// K-tiles on their way through its pipeline (7001 x 5458 x 94: 105 us against
+// 123 on the best split tile, 1463 x 1664 x 64: 9.0 against 10.1; 1168 x 1600
+// x 126: 10.6 against 9.4, from K = 120 never behind by more than 3%).
+constexpr int64_t kSplitMinK = 120;
 
 // Built-in choice for slots the table does not hold: for the FP32 products
 // the split tiles, and with a short reduction one of the shapes the search
-// picked for the FP32 cores; for the symmetric contractions, the
-// stream-K schedule for a long reduction or a large result.
+// picked for the FP32 cores; the symmetric contractions likewise.
 int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
 {
     const int64_t cus = 256;  // compute units of an MI355X
@@ -119,24 +118,36 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         return side <= 8 ? 2 : side <= 11 ? 20 : side == 12 ? 44 : 49;
     }
     if (kernel == LI_KERNEL_SYRK_F32) {
-        // M features (the order of the result), K samples.  The search
-        // picks the 128 x 128 stream-K schedule (or its eight-wave form,
-        // within 2%) for every order from 2048 to 4096: 1.5x faster than
-        // one 128 x 128 tile per work-group at 4096, where the upper
-        // triangle has twice as many tiles as there are compute units.
-        // Short reductions over small results take 64 x 64 tiles.
-        if (M >= 2048 || K >= 1024) return 20;  // 128 x 128 stream-K, 16 waves
-        return 17;                              // 64 x 64, direct loads, 3-stage ring
+        // M features (the order of the result), K samples.  Measured over
+        // 136 shapes with M log-uniform from 32 to 4096 and K from 64 to
+        // 32768 (times with the statistics): the picks are within 2% of the
+        // fastest candidate on average.  Few samples: FP32 cores (3776 x 128:
+        // 38 us against 47 on the best split tile; 320 x 211 from 17.5 to 17.0).
+        // A small result with a short reduction: one wave per 32 x 32 tile
+        // (512 x 512: 20.6 us against 23.5 in 64 x 64 phases; 631 x 745 the
+        // other way, 25.7 and 23.4).  Otherwise phases, of 128 x 128 tiles
+        // where the work outweighs their longer pipeline (1024 x 2048, 2.1e9
+        // products: 39.1 us against 41.4 in 64 x 64; 896 x 1216, 1e9: 34.9 and 31.7).
+        if (K <= 200) return 17;
+        if (M <= 704 && K < 700) return 27;
+        return (double)M * (double)M * (double)K >= 2e9 ? 20 : 21;
     }
     if (kernel == LI_KERNEL_SYRK_ROWS) {
-        // M is the order of C, K the reduction length (the rank).  The
-        // search picks stream-K at every order from 2048 to 4096 unless
-        // the rank is short (1.4x faster than one 128 x 128 tile per
-        // work-group at 4096, rank 4096), unsplit 64 x 64 tiles for a
-        // short rank, and 64 x 64 tiles split in four below.
-        if (4 * K < 3 * M) return 10;            // 64 x 64, one work-group per tile
-        if (M >= 2048 || K >= 4096) return 15;   // 128 x 128 stream-K, 16 waves
-        return 9;                                // 64 x 64, split in four
+        // M is the order of C, K the reduction length (the rank).  Over 156
+        // shapes (both updates, M from 128 to 4096, K from 64 to 8192): a
+        // large result of a short rank on the FP32 cores (4096 x 128: syrk
+        // 38.8 us against 43.1), a small one in 32 x 32 tiles (512 x 384: 9.1
+        // us against 11.1 in 64 x 64; 336 x 779 the other way, 14.6 and 12.6).
+        // Otherwise phases, of 128 x 128 tiles where the work outweighs
+        // their pipeline (2048 x 2048: 62.7 us against 67.1 in 64 x 64, syr2k
+        // 108 and 126; 1024 x 1024 21.5 and 20.7; 4096 x 512 101 and 81), or
+        // without cut tiles, which need no scratch, where eight rounds of them
+        // hide the last one (8192 x 1024: 0.518 ms against 0.508; 6500 x 1500
+        // 0.437 and 0.408).
+        if (M >= 2048 && K < 160) return 16;
+        if (M <= 1152 && K < 700) return 17;
+        if (M >= 8192 && 4 * K < 3 * M) return 10;
+        return K >= 640 && (double)M * (double)M * (double)K >= 2.5e9 ? 15 : 14;
     }
     if (kernel == LI_KERNEL_GROUPED_GEMM || kernel == LI_KERNEL_GROUPED_COV) {
         // the 128 class when the output has at least 256 rows and columns
