@@ -30,7 +30,13 @@ __global__ __launch_bounds__(T::NT) void gemm_f32_kernel(const float *__restrict
     const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
-    if (alpha != 0.f) T::mainloop(lds, A, lda, B, ldb, M, N, 0, K, m0, n0, acc);
+    if constexpr (T::SPLIT) {
+        const auto warm = T::warm_c(C, ldc, M, N, m0, n0, beta);
+        if (alpha != 0.f) T::mainloop(lds, A, lda, B, ldb, M, N, 0, K, m0, n0, acc);
+        warm.touch();
+    } else {
+        if (alpha != 0.f) T::mainloop(lds, A, lda, B, ldb, M, N, 0, K, m0, n0, acc);
+    }
     T::store_c(lds, acc, C, ldc, M, N, m0, n0, alpha, beta);
 }
 

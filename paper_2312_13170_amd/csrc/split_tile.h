@@ -182,50 +182,74 @@ struct SplitLoader {
         }
     }
 
-    // base: the first element of this K-tile (see places); left: k values
-    // that remain from there (values past them are 0, or `fill`, which the
-    // transform maps to 0).  FULL: a whole K-tile of at least CW rows.
-    template <bool FULL>
-    __device__ __forceinline__ void load(const float *__restrict__ base, const uint32_t (&off)[PER], int64_t ld,
-                                         int64_t left, int64_t rows, const float (&fill)[PER][CW], int tid)
+    // A whole K-tile, base its first element (see places).  Buffer loads: a
+    // uniform descriptor of this K-tile, the lane's 32-bit offset and a uniform
+    // row offset, so no vector instruction forms an address.
+    __device__ __forceinline__ void load(const float *__restrict__ base, const uint32_t (&off)[PER], int64_t ld)
     {
-        // buffer loads: a uniform descriptor of this K-tile, the lane's 32-bit
-        // offset and a uniform row offset, so no vector instruction forms an
-        // address
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, 0xffffffff, 0x00027000);
         const int ld4 = (int)ld * 4;
-        if constexpr (FULL) {
 #pragma unroll
-            for (int i = 0; i < PER; ++i) {
-                if constexpr (KMAJOR) {
+        for (int i = 0; i < PER; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const auto raw = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], j * ld4, 0);
-                        v[i][j] = __builtin_bit_cast(f32x4, raw);
-                    }
-                } else {
-                    const auto raw = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], 0, 0);
-                    v[i][0] = __builtin_bit_cast(f32x4, raw);
-                }
+            for (int j = 0; j < CW; ++j) {
+                const auto raw = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[i], j * ld4, 0);
+                v[i][j] = __builtin_bit_cast(f32x4, raw);
             }
-        } else {
+    }
+
+    // The same, element by element: `left` k values remain from base (those
+    // past them are 0, or `fill`, which the transform maps to 0), of a k-major
+    // operand of fewer than CW rows.
+    __device__ __forceinline__ void load_checked(const float *__restrict__ base, const uint32_t (&off)[PER], int64_t ld,
+                                                 int64_t left, int64_t rows, const float (&fill)[PER][CW], int tid)
+    {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, 0xffffffff, 0x00027000);
+        const int ld4 = (int)ld * 4;
 #pragma unroll
-            for (int i = 0; i < PER; ++i)
+        for (int i = 0; i < PER; ++i)
 #pragma unroll
-                for (int e = 0; e < CW; ++e)
+            for (int j = 0; j < CW; ++j)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        float x = XFORM ? fill[i][e] : 0.f;
-                        if (piece_k(tid + i * NT) + j < left && e < rows)
-                            x = __builtin_bit_cast(
-                                float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off[i] + (KMAJOR ? 4 * e : 4 * j),
-                                                                            KMAJOR ? j * ld4 : 0, 0));
-                        if (KMAJOR)
-                            v[i][KMAJOR ? j : 0][e] = x;
-                        else
-                            v[i][0][j] = x;
-                    }
-        }
+                for (int e = 0; e < CW; ++e) {
+                    float x = XFORM ? fill[i][e] : 0.f;
+                    if (piece_k(tid + i * NT) + j < left && e < rows)
+                        x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, off[i] + 4 * e, j * ld4, 0));
+                    v[i][j][e] = x;
+                }
+    }
+
+    // A partial K-tile: `left` k values from base on, the matrix ending at
+    // `bytes` from there.  16-byte loads as in a whole K-tile; a piece past
+    // `left` gets an offset out of the descriptor's range, where loads return 0,
+    // as they do for the elements of the last row's last piece past the end.
+    __device__ __forceinline__ void load_part(const float *__restrict__ base, const uint32_t (&off)[PER], int64_t ld,
+                                              int left, int64_t bytes, int tid)
+    {
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0,
+                                                            (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00027000);
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+#pragma unroll
+            for (int j = 0; j < CW; ++j) {
+                const uint32_t o = off[i] + (KMAJOR ? (uint32_t)j * (uint32_t)ld * 4u : 0u);
+                const auto raw = __builtin_amdgcn_raw_buffer_load_b128(
+                    rsrc, piece_k(tid + i * NT) + (KMAJOR ? j : 0) < left ? o : 0xfffffff0u, 0, 0);
+                v[i][j] = __builtin_bit_cast(f32x4, raw);
+            }
+    }
+
+    // (values past `left` become 0, or `fill`, which the transform maps to 0)
+    __device__ __forceinline__ void mask(int left, const float (&fill)[PER][CW], int tid)
+    {
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+#pragma unroll
+            for (int j = 0; j < CW; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (piece_k(tid + i * NT) + (KMAJOR ? j : e) >= left)
+                        v[i][j][e] = XFORM ? fill[i][KMAJOR ? e : 0] : 0.f;
     }
 
     __device__ __forceinline__ void store(uint16_t *lds, const int (&at)[PER][CW], uint32_t &lost,
@@ -389,13 +413,13 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
                 }
     }
 
-    // Matrix waves: hi, lo += the products of nk K-tiles.
-    __device__ __forceinline__ static void multiply(const uint16_t *lds, int nk, f32x16 (&hi)[TM][TN],
+    // Matrix waves: hi, lo += the products of nk K-tiles, the first in stage s0.
+    __device__ __forceinline__ static void multiply(const uint16_t *lds, int nk, int s0, f32x16 (&hi)[TM][TN],
                                                     f32x16 (&lo)[TM][TN])
     {
         const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
         const int wm0 = (w / WN) * (BM / WM), wn0 = (w % WN) * (BN / WN);
-        const uint16_t *cur = lds, *nxt = lds + STAGE;
+        const uint16_t *cur = lds + s0 * STAGE, *nxt = lds + (1 - s0) * STAGE;
         Frag f, g;
         __builtin_amdgcn_s_setprio(1);
         lds_barrier();  // K-tile 0 is stored
@@ -425,15 +449,14 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
 
     // Splitting waves of one operand (L; tile at row r0 of `rows`): nk K-tiles
     // into its part of the two stages in turn, loaded two K-tiles ahead of
-    // their split.
-    // P1: the operand of a second product over the same k, or NULL
-    // (k-contiguous operands only): the whole K-tiles of both, then the
-    // partial ones, in one run of the pipeline.
+    // their split.  P1: the operand of a second product over the same k, or
+    // NULL (k-contiguous operands only).  The partial K-tiles (np, one of each
+    // product) come first, into the stages that leave the whole ones starting
+    // at stage 0; their loads are in flight with those of the first whole ones.
     template <class L, bool KMAJOR>
     __device__ __forceinline__ static void produce(uint16_t *lds, const float *P, const float *P1, int64_t ld,
-                                                   int64_t rows,
-                                                   int64_t kbeg, int64_t kend, int64_t r0, int nk, int tid,
-                                                   uint32_t &lost, const XRegs *xr)
+                                                   int64_t rows, int64_t kbeg, int64_t kend, int64_t r0, int nk,
+                                                   int np, int tid, uint32_t &lost, const XRegs *xr)
     {
         float m[L::PER][L::CW], f[L::PER][L::CW];
         columns<L>(xr, rows, r0, tid, m, f);
@@ -441,48 +464,63 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
         uint32_t off[L::PER];
         int at[L::PER][L::CW];
         L::places(off, at, ld, rows, r0, tid);
-        const int64_t adv = KMAJOR ? BK * ld : BK;
-        const float *p = KMAJOR ? P + kbeg * ld : P + r0 * ld + kbeg;
+        const int64_t adv = KMAJOR ? BK * ld : BK, first = KMAJOR ? kbeg * ld : r0 * ld + kbeg;
         // Whole K-tiles run a loop without branches around its loads, so the
         // waits count them exactly; loads past the last whole K-tile repeat
-        // it.  A partial one (or a k-major operand of fewer than CW rows)
-        // takes checked loads.  Code that runs once per block tile is kept
-        // short: its instructions come from memory.
-        const int n1 = (int)((kend - kbeg) / BK);
-        const int nfast = KMAJOR && rows < L::CW ? 0 : P1 ? 2 * n1 : n1;
-        const float *p1 = P1 ? P1 + r0 * ld + kbeg : p;
+        // it.  Code that runs once per block tile is kept short: its
+        // instructions come from memory.
+        const int n1 = (int)((kend - kbeg) / BK), left = (int)((kend - kbeg) % BK);
+        auto store = [&](int set, int stage) { l[set].store(lds + (stage & 1) * STAGE, at, lost, m, f); };
+        if (KMAJOR && rows < L::CW) {
+            // too few rows for 16-byte loads
+            for (int t = 0; t < nk; ++t) {
+                const int64_t kt = t < np ? n1 : t - np;
+                l[0].load_checked(P + first + kt * adv, off, ld, kend - kbeg - kt * BK, rows, m, tid);
+                store(0, t + np);
+                lds_barrier();
+            }
+            lds_barrier();
+            return;
+        }
+        const int nfast = nk - np;
+        const float *p = P + first;
         int loaded = 0;
         auto load = [&](int set) {
-            l[set].template load<true>(p, off, ld, 0, rows, m, tid);
+            l[set].load(p, off, ld);
             ++loaded;
             p += loaded < nfast ? adv : 0;
-            if (loaded == n1 && P1) p = p1;
+            if (!KMAJOR && P1 && loaded == n1) p = P1 + first;
             __builtin_amdgcn_sched_barrier(0);
         };
-        auto store = [&](int set, int t) { l[set].store(lds + (t & 1) * STAGE, at, lost, m, f); };
+        auto load_part = [&](const float *q) {
+            const int64_t last = KMAJOR ? (kend - 1) * ld + rows : (rows - 1) * ld + kend;
+            l[0].load_part(q + first + n1 * adv, off, ld, left, (last - first - n1 * adv) * 4, tid);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if (np > 0) load_part(P);
+        if (nfast > 0) load(1);
+#pragma unroll 1
+        for (int t = 0; t < np; ++t) {
+            if (!KMAJOR && t > 0) load_part(P1);
+            l[0].mask(left, m, tid);
+            store(0, t + np);
+            lds_barrier();
+        }
         if (nfast > 0) {
             load(0);
-            load(1);
-        }
-        int t = 0;
-        for (; t + 2 <= nfast; t += 2) {
-            store(0, 0);
-            load(0);
-            lds_barrier();  // K-tile t is stored, the one before is read
-            store(1, 1);
-            load(1);
-            lds_barrier();
-        }
-        const float *q = KMAJOR ? P + kbeg * ld : P + r0 * ld + kbeg;
-        for (; t < nk; ++t) {
-            if (t >= nfast) {
-                // K-tile of its product: every one (too few rows), or the partial one
-                const int64_t kt = KMAJOR && nfast == 0 ? t : n1;
-                l[0].template load<false>((t > nfast && !KMAJOR ? p1 : q) + kt * adv, off, ld,
-                                          kend - kbeg - kt * BK, KMAJOR ? rows : 1, m, tid);
+            int t = 0;
+            for (; t + 2 <= nfast; t += 2) {
+                store(1, 0);
+                load(1);
+                lds_barrier();  // K-tile t is stored, the one before is read
+                store(0, 1);
+                load(0);
+                lds_barrier();
             }
-            store(0, t);
-            lds_barrier();
+            if (t < nfast) {
+                store(1, 0);
+                lds_barrier();
+            }
         }
         lds_barrier();
     }
@@ -495,16 +533,17 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
                                                   f32x16 (&hi)[TM][TN], f32x16 (&lo)[TM][TN], uint32_t &lost,
                                                   const XRegs *xr)
     {
-        const int nk = (int)((kend - kbeg + BK - 1) / BK) * (A1 ? 2 : 1);
+        const int two = A1 ? 2 : 1, nk = (int)((kend - kbeg + BK - 1) / BK) * two;
+        const int np = (kend - kbeg) % BK ? two : 0;
         // nk + 1 barriers on every side
         const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) - WM * WN;
         if (w < 0)
-            multiply(lds, nk, hi, lo);
+            multiply(lds, nk, np & 1, hi, lo);
         else if (w < PWA)
-            produce<LA, A_KMAJOR>(lds, A, A1, lda, M, kbeg, kend, m0, nk, (int)threadIdx.x - ET, lost, xr);
+            produce<LA, A_KMAJOR>(lds, A, A1, lda, M, kbeg, kend, m0, nk, np, (int)threadIdx.x - ET, lost, xr);
         else
-            produce<LB, !B_NMAJOR>(lds + 3 * LA::PART, B, B1, ldb, N, kbeg, kend, n0, nk, (int)threadIdx.x - ET - 64 * PWA,
-                                   lost, xr);
+            produce<LB, !B_NMAJOR>(lds + 3 * LA::PART, B, B1, ldb, N, kbeg, kend, n0, nk, np,
+                                   (int)threadIdx.x - ET - 64 * PWA, lost, xr);
     }
 
     // acc += A B on the FP32 matrix cores: the matrix waves run the FP32
@@ -604,6 +643,32 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     lds[acc_row(wm0, i, v, lane) * OLD + acc_col(wn0, j, lane)] = acc[i][j][v];
+    }
+
+    // One element of each line of the tile of C, for store_c to find them in
+    // the L2: read by the matrix waves before the main loop, used (touched)
+    // after it, which otherwise would wait for memory once more at its end.
+    static constexpr int WARM = (BM * (BN / 32) + ET - 1) / ET;
+    struct WarmC {
+        float x[WARM];
+        __device__ __forceinline__ void touch() const
+        {
+#pragma unroll
+            for (int i = 0; i < WARM; ++i) asm volatile("" ::"v"(x[i]));
+        }
+    };
+    __device__ __forceinline__ static WarmC warm_c(const float *C, int64_t ldc, int64_t M, int64_t N, int64_t m0,
+                                                   int64_t n0, float beta)
+    {
+        WarmC w;
+#pragma unroll
+        for (int i = 0; i < WARM; ++i) {
+            const int line = (int)threadIdx.x + i * ET;
+            const int64_t row = m0 + line / (BN / 32), col = n0 + line % (BN / 32) * 32;
+            w.x[i] = 0.f;
+            if (beta != 0.f && active() && line < BM * (BN / 32) && row < M && col < N) w.x[i] = C[row * ldc + col];
+        }
+        return w;
     }
 
     // C = alpha acc + beta C over the in-range part of the tile (beta == 0: C
