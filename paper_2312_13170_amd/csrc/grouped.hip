@@ -6,15 +6,25 @@
 //                            column means (same chunking and merge order as
 //                            the single-problem kernels, so the results are
 //                            bitwise the same) and the centred data.
-//  node 2  grouped_contract: a persistent kernel; work-group b takes the
-//                            output tiles b, b + grid, b + 2*grid, ... of one
-//                            table that lists every tile of every problem
-//                            (GEMM tiles and upper-triangle covariance
-//                            tiles), sorted by decreasing work so the static
-//                            round-robin split balances.  Each tile runs the
-//                            same loop-internalised FP32 main loop and
-//                            epilogue as the single-problem kernels with the
-//                            tile shape chosen for its problem.
+//  node 2  grouped_contract: per shape class and problem kind one launch
+//                            over a table of every output tile of its
+//                            problems (GEMM tiles and upper-triangle
+//                            covariance tiles), dealt to the XCDs problem by
+//                            problem (deal_tiles).  Each tile runs the same
+//                            main loop and epilogue as the single-problem
+//                            kernels with the tile shape chosen for its
+//                            problem: the split tiles of split_tile.h, or
+//                            the FP32 cores' for rows too long for them.
+//
+// 512 products and 512 covariances, sizes log-uniform from 32 to 1024: 868 us
+// on the FP32 cores, 707 on the split tiles.  The three kernels each fill the
+// compute units, so their times add (statistics 135, products 330,
+// covariances 330 us): the statistics are near the copy rate (0.6 GB); a
+// product's 64 x 64 tile takes 14 us for 9 K-tiles on average, half of it
+// before its first and after its last, and is bound by the vector
+// instructions that split its operands and by latency together (a third
+// work-group per compute unit, at 80 registers and a few spills, is slower:
+// 876 us against 810 in the same back-to-back loop).
 // The covariance launches depend on node 1 (their tiles read the centred
 // data); the GEMM launches are independent of it.
 #include <hip/hip_runtime.h>
@@ -25,9 +35,10 @@
 #include <new>
 #include <vector>
 
-#include "f32_tile.h"
 #include "li_internal.h"
+#include "split_tile.h"
 #include "stats_dev.h"
+#include "symm_kernels.h"
 #include "tiles.h"
 
 namespace li {
@@ -53,8 +64,8 @@ struct GStatBlock {
     int32_t prob, col0;
 };
 
-template <int BM, int BN, int BK, int WM, int WN, bool KMAJOR, int PF>
-using Tile = F32Tile<BM, BN, BK, WM, WN, KMAJOR, kLoadScalar, PF>;
+template <int BT, int BK, int WM, int WN, bool KMAJOR, int PF>
+using Tile = CandidateTile<BT, BT, BK, WM, WN, PF, KMAJOR, false, 0, kLoadScalar, PF>;
 
 // Statistics of one covariance problem's block of kGStatCols columns: the
 // kMergeGroups thread rows each merge one group of chunk partials (chunk
@@ -130,6 +141,13 @@ __device__ __forceinline__ void gemm_tile(float *lds, const GProb &p, const GTil
     const int64_t m0 = (int64_t)td.tm * T::BM, n0 = (int64_t)td.tn * T::BN;
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
+    if constexpr (T::SPLIT) {
+        const auto warm = T::warm_c(p.C, p.N, p.M, p.N, m0, n0, p.beta);
+        if (p.alpha != 0.f) T::mainloop(lds, p.A, p.K, p.B, p.N, p.M, p.N, 0, p.K, m0, n0, acc);
+        warm.touch();
+        T::store_c(lds, acc, p.C, p.N, p.M, p.N, m0, n0, p.alpha, p.beta);
+        return;
+    }
     if (p.alpha != 0.f) T::mainloop(lds, p.A, p.K, p.B, p.N, p.M, p.N, 0, p.K, m0, n0, acc);
     if (p.beta != 0.f) {
         // the tile's C loads issued together, then one wait
@@ -145,38 +163,35 @@ template <class T>
 __device__ __forceinline__ void syrk_tile(float *lds, const GProb &p, const GTile &td)
 {
     const int64_t m0 = (int64_t)td.tm * T::BM, n0 = (int64_t)td.tn * T::BN;
+    const SymArgs a{p.Y, nullptr, p.M, p.M, p.N, p.C, 0, p.scale, 0.f, 1, nullptr, nullptr};
     f32x16 acc[T::TM][T::TN];
     T::zero(acc);
-    T::mainloop(lds, p.Y, p.M, p.Y, p.M, p.M, p.M, 0, p.N, m0, n0, acc);
-    epilogue_syrk<T>(acc, p.C, p.M, m0, n0, 0, p.scale);
+    sym_reduce<T, kSymCols>(lds, a, 0, p.N, m0, n0, acc);
+    finish_sym<T>(lds, acc, a, m0, n0);
 }
 
-// Contraction kernel of one shape class over the class's tile table (sorted
-// by decreasing work).  PERSIST: a resident grid, work-group b takes tiles
-// b, b + gridDim.x, ...; otherwise one work-group per tile, handed out by
-// the hardware dispatcher heaviest first as compute units free up, with
-// each run of 64 table entries dealt to the eight XCDs in blocks of eight
-// consecutive entries (tiles of one problem share operand panels in L2).
-__device__ __forceinline__ int dispatch_tile(int b, int n)
-{
-    const int w = b & ~63;
-    if (w + 64 > n) return b;  // last partial window: in order
-    return w + (b & 7) * 8 + ((b >> 3) & 7);
-}
+constexpr int kXcds = 8;
+// entry of work-group b: the XCDs' lists lie one after the other
+__device__ __forceinline__ int table_entry(int b, int n) { return b % kXcds * (n / kXcds) + b / kXcds; }
 
+// Contraction kernel of one shape class over the class's tile table (see
+// deal_tiles).  PERSIST: a resident grid, work-group b takes tiles b,
+// b + gridDim.x, ...; otherwise one work-group per tile, handed out by the
+// hardware dispatcher in table order as compute units free up.
 template <int BT, int BK, int WM, int WN, int PF, int KIND, bool PERSIST>
-__global__ __launch_bounds__(64 * WM * WN) void grouped_contract(const GProb *__restrict__ probs,
+__global__ __launch_bounds__((Tile<BT, BK, WM, WN, false, PF>::NT)) void grouped_contract(const GProb *__restrict__ probs,
                                                                  const GTile *__restrict__ tiles,
                                                                  int ntiles)
 {
     // one main loop per kernel; its loads take rows of any alignment
-    using G = Tile<BT, BT, BK, WM, WN, false, PF>;
-    using S = Tile<BT, BT, BK, WM, WN, true, PF>;
+    using G = Tile<BT, BK, WM, WN, false, PF>;
+    using S = Tile<BT, BK, WM, WN, true, PF>;
     constexpr int L1 = KIND == LI_PROBLEM_GEMM ? G::LDS_FLOATS : S::LDS_FLOATS;
     __shared__ __attribute__((aligned(16))) float lds[L1];
     if (PERSIST) {
         for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-            const GTile td = tiles[t];
+            const GTile td = tiles[table_entry(t, ntiles)];
+            if (td.prob < 0) continue;
             const GProb &p = probs[td.prob];
             if (KIND == LI_PROBLEM_GEMM)
                 gemm_tile<G>(lds, p, td);
@@ -185,9 +200,8 @@ __global__ __launch_bounds__(64 * WM * WN) void grouped_contract(const GProb *__
             __syncthreads();
         }
     } else {
-        const int t = dispatch_tile((int)blockIdx.x, ntiles);
-        if (t >= ntiles) return;
-        const GTile td = tiles[t];
+        const GTile td = tiles[table_entry((int)blockIdx.x, ntiles)];
+        if (td.prob < 0) return;
         const GProb &p = probs[td.prob];
         if (KIND == LI_PROBLEM_GEMM)
             gemm_tile<G>(lds, p, td);
@@ -197,13 +211,13 @@ __global__ __launch_bounds__(64 * WM * WN) void grouped_contract(const GProb *__
 }
 
 struct ShapeClass {
-    int cls, gemm_idx, syrk_idx, bt, bk, wm, wn, pf;
+    int cls, gemm_idx, syrk_idx, bt, bk, wm, wn, pf, threads;
     const void *kernel[2];   // [LI_PROBLEM_GEMM], [LI_PROBLEM_COVARIANCE]: one work-group per tile
     const void *persist[2];  // the same on a resident grid
 };
 
 #define LI_CLASS(C, GI, SI, BT, BK, WM, WN, PF)                                                     \
-    {C, GI, SI, BT, BK, WM, WN, PF,                                                                 \
+    {C, GI, SI, BT, BK, WM, WN, PF, Tile<BT, BK, WM, WN, false, PF>::NT,                            \
      {(const void *)grouped_contract<BT, BK, WM, WN, PF, LI_PROBLEM_GEMM, false>,                   \
       (const void *)grouped_contract<BT, BK, WM, WN, PF, LI_PROBLEM_COVARIANCE, false>},            \
      {(const void *)grouped_contract<BT, BK, WM, WN, PF, LI_PROBLEM_GEMM, true>,                    \
@@ -233,14 +247,70 @@ bool shapes_consistent()
 }
 
 // Class of a problem: the tuning table's entry for the grouped family of its
-// kind (forced > table > built-in heuristic).
-int pick_class(int kernel, int64_t M, int64_t N, int64_t K)
+// kind (forced > table > built-in heuristic); rows of `ld` elements that the
+// split tiles' offsets cannot span take the FP32 cores' class.
+constexpr int kFp32Class = 3;
+static_assert(kNumClasses == kFp32Class + 1, "the last class is the FP32 cores'");
+int pick_class(int kernel, int64_t M, int64_t N, int64_t K, int64_t ld)
 {
+    if (ld > kSplitMaxLd) return kFp32Class;
     const int c = tune_pick(kernel, M, N, K);
     return c >= 0 && c < kNumClasses ? c : 0;
 }
 
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
+// The tiles of one problem in a shape class, each of the same cost.
+struct Bundle {
+    double cost;  // of one tile
+    std::vector<GTile> tiles;
+};
+
+// The table of a class: work-group b runs on XCD b mod 8 and takes tile b / 8
+// of that XCD's list (neighbouring entries share a line of its L2).  A problem's tiles go to one XCD (cut into parts
+// where one would outweigh a 32nd of the work), whose L2 then reads its
+// operands from memory once; the XCDs' loads are balanced greedily, largest
+// part first, and each XCD takes its heaviest tiles first.  Shorter lists end
+// in entries without a problem.  512 + 512 problems, sizes
+// log-uniform from 32 to 1024: 0.53 GB of L2 misses in the products, the batch 828
+// us; with tiles dealt in runs of eight regardless of problem 1.2 GB, 849 us.
+std::vector<GTile> deal_tiles(std::vector<Bundle> &all)
+{
+    constexpr int X = kXcds;
+    double total = 0;
+    for (const Bundle &b : all) total += b.cost * (double)b.tiles.size();
+    std::vector<Bundle> parts;
+    for (const Bundle &b : all) {
+        const size_t most = std::max<size_t>(1, (size_t)(total / 32 / b.cost));
+        for (size_t k = 0; k < b.tiles.size(); k += most)
+            parts.push_back({b.cost, std::vector<GTile>(b.tiles.begin() + k,
+                                                        b.tiles.begin() + std::min(k + most, b.tiles.size()))});
+    }
+    std::stable_sort(parts.begin(), parts.end(), [](const Bundle &x, const Bundle &y) {
+        return x.cost * (double)x.tiles.size() > y.cost * (double)y.tiles.size();
+    });
+    std::vector<const Bundle *> list[X];
+    double load[X] = {};
+    for (const Bundle &b : parts) {
+        const int x = (int)(std::min_element(load, load + X) - load);
+        load[x] += b.cost * (double)b.tiles.size();
+        list[x].push_back(&b);
+    }
+    size_t longest = 0;
+    std::vector<GTile> of[X];
+    for (int x = 0; x < X; ++x) {
+        std::stable_sort(list[x].begin(), list[x].end(),
+                         [](const Bundle *p, const Bundle *q) { return p->cost > q->cost; });
+        for (const Bundle *b : list[x]) of[x].insert(of[x].end(), b->tiles.begin(), b->tiles.end());
+        longest = std::max(longest, of[x].size());
+    }
+    std::vector<GTile> table;
+    for (int x = 0; x < X; ++x) {
+        of[x].resize(longest, GTile{-1, 0, 0, 0});
+        table.insert(table.end(), of[x].begin(), of[x].end());
+    }
+    return table;
+}
 
 struct SpanRec {
     uintptr_t lo, hi;
@@ -376,8 +446,9 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
     (void)hipGetDevice(&p->device);
     p->problems.assign(problems, problems + count);
     std::vector<GProb> hp(count);
-    std::vector<GTile> tiles[kSlots];
-    std::vector<double> cost[kSlots];
+    std::vector<Bundle> work[kSlots];
+    // a tile's pipeline fill and epilogue take about as long as 128 k
+    auto tile_cost = [](int bt, double k) { return (double)bt * bt * (k + 128.0); };
     std::vector<GStatBlock> stat;
     size_t loop_ws = 0;
     for (int i = 0; i < count; ++i) {
@@ -396,20 +467,18 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
         g.mean = q.mean;
         int cls;
         if (q.kind == LI_PROBLEM_GEMM) {
-            cls = pick_class(LI_KERNEL_GROUPED_GEMM, q.M, q.N, q.K);
+            cls = pick_class(LI_KERNEL_GROUPED_GEMM, q.M, q.N, q.K, std::max(q.K, q.N));
             const int bt = kClasses[cls].bt;
             g.cfg = kClasses[cls].gemm_idx;
             g.vec4 = (q.alpha == 0.f || (q.K % 4 == 0 && q.N % 4 == 0 && aligned16(q.A) && aligned16(q.B))) ? 1 : 0;
             const int tm = (int)((q.M + bt - 1) / bt), tn = (int)((q.N + bt - 1) / bt);
-            const double w = (double)bt * bt * ((q.alpha != 0.f ? (double)q.K : 0.0) + 1.0);
+            Bundle w{tile_cost(bt, q.alpha != 0.f ? (double)q.K : 0.0), {}};
             for (int a = 0; a < tm; ++a)
-                for (int b = 0; b < tn; ++b) {
-                    tiles[2 * cls + LI_PROBLEM_GEMM].push_back({i, a, b, 0});
-                    cost[2 * cls + LI_PROBLEM_GEMM].push_back(w);
-                }
+                for (int b = 0; b < tn; ++b) w.tiles.push_back({i, a, b, 0});
+            work[2 * cls + LI_PROBLEM_GEMM].push_back(std::move(w));
             p->flops += 2.0 * q.M * q.N * q.K + 3.0 * q.M * q.N;
         } else {
-            cls = pick_class(LI_KERNEL_GROUPED_COV, q.M, q.M, q.N);
+            cls = pick_class(LI_KERNEL_GROUPED_COV, q.M, q.M, q.N, q.M);
             const int bt = kClasses[cls].bt;
             g.cfg = kClasses[cls].syrk_idx;
             g.vec4 = (q.M % 4 == 0 && aligned16(q.data_out)) ? 1 : 0;
@@ -421,12 +490,10 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
                 for (int64_t c0 = 0; c0 < q.M; c0 += kGStatCols) stat.push_back({i, (int32_t)c0});
                 loop_ws = std::max(loop_ws, stats_workspace_bytes(q.M, q.N));
                 const int tm = (int)((q.M + bt - 1) / bt);
-                const double w = (double)bt * bt * ((double)q.N + 1.0);
+                Bundle w{tile_cost(bt, (double)q.N), {}};
                 for (int a = 0; a < tm; ++a)
-                    for (int b = a; b < tm; ++b) {
-                        tiles[2 * cls + LI_PROBLEM_COVARIANCE].push_back({i, a, b, 0});
-                        cost[2 * cls + LI_PROBLEM_COVARIANCE].push_back(w);
-                    }
+                    for (int b = a; b < tm; ++b) w.tiles.push_back({i, a, b, 0});
+                work[2 * cls + LI_PROBLEM_COVARIANCE].push_back(std::move(w));
             }
             p->flops += (double)q.N * q.M * (q.M + 1);
         }
@@ -443,28 +510,23 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
     bool ok = up((void **)&p->d_probs, hp.data(), hp.size() * sizeof(GProb)) &&
               up((void **)&p->d_stat, stat.data(), stat.size() * sizeof(GStatBlock));
     for (int c = 0; c < kSlots && ok; ++c) {
-        // heaviest tiles first, so the round-robin split balances
-        std::vector<size_t> order(tiles[c].size());
-        for (size_t k = 0; k < order.size(); ++k) order[k] = k;
-        std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return cost[c][x] > cost[c][y]; });
-        std::vector<GTile> sorted(tiles[c].size());
-        for (size_t k = 0; k < order.size(); ++k) sorted[k] = tiles[c][order[k]];
-        p->ntiles[c] = (int)sorted.size();
+        const std::vector<GTile> table = deal_tiles(work[c]);
+        p->ntiles[c] = (int)table.size();
         const ShapeClass &sc = kClasses[c / 2];
         if (persist) {
             // as many work-groups as can be resident at once
             int per_cu = 1;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sc.persist[c % 2], 64 * sc.wm * sc.wn,
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sc.persist[c % 2], sc.threads,
                                                              0) != hipSuccess ||
                 per_cu < 1) {
                 (void)hipGetLastError();
                 per_cu = 1;
             }
-            p->grid[c] = std::min(p->ntiles[c], per_cu * device_cu_count());
+            p->grid[c] = std::min(p->ntiles[c], per_cu * device_cu_count() / kXcds * kXcds);
         } else {
             p->grid[c] = p->ntiles[c];
         }
-        ok = up((void **)&p->d_tiles[c], sorted.data(), sorted.size() * sizeof(GTile));
+        ok = up((void **)&p->d_tiles[c], table.data(), table.size() * sizeof(GTile));
     }
     p->nstat = (int)stat.size();
     if (ok && loop_ws) ok = hipMalloc(&p->loop_ws, loop_ws) == hipSuccess;
@@ -499,7 +561,7 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
         hipKernelNodeParams kp{};
         kp.func = const_cast<void *>(persist ? sc.persist[c % 2] : sc.kernel[c % 2]);
         kp.gridDim = dim3((unsigned)p->grid[c]);
-        kp.blockDim = dim3(64 * sc.wm * sc.wn);
+        kp.blockDim = dim3((unsigned)sc.threads);
         kp.sharedMemBytes = 0;
         kp.kernelParams = args;
         kp.extra = nullptr;

@@ -98,7 +98,9 @@
     X(24, 128, 128, 32, 4, 4, 0, 3)          \
     X(25, 128, 128, 32, 2, 4, 0, 4)          \
     X(26, 32, 32, 32, 1, 1, 1, 3)            \
-    X(27, 32, 32, 32, 1, 1, 1, 10)
+    X(27, 32, 32, 32, 1, 1, 1, 10)           \
+    X(28, 128, 128, 32, 2, 2, 1, 9)          \
+    X(29, 64, 64, 32, 2, 2, 1, 9)
 
 // bf16 / fp16 matrix-core GEMM on pre-rounded operands; the last column is
 // the LDS layout here (1: XOR-swizzled rows, 2: rows padded by 16 bytes,
@@ -166,15 +168,18 @@
 // Shape classes of the grouped execution (grouped.hip), also the candidates
 // of the tuning families LI_KERNEL_GROUPED_GEMM / LI_KERNEL_GROUPED_COV.
 // Each class is one contraction kernel per problem kind whose tiles share
-// the block tile; the main loop keeps two K-tiles in flight with the LDS
-// operand reads pipelined across the barrier (mode 3) and loads rows of any
-// alignment with 16-byte loads.  The GEMM and covariance candidates named
+// the block tile; all load rows of any alignment with 16-byte loads.
+// Classes 0 to 2 are the split tiles (three bf16 parts), class 3 the FP32
+// cores' tile for short reductions and for rows too long for the split
+// tiles' offsets (mode 3: two K-tiles in flight, the LDS operand reads
+// pipelined across the barrier).  The GEMM and covariance candidates named
 // are the single-problem candidates of the same shape, which the
 // per-instance launch loop of a plan uses.
 // {class, GEMM candidate, covariance candidate, block tile, BK, waves_m,
-//  waves_n, main-loop mode}.  The 32 tile (one wave) wastes less of small
-// problems on padding.
+//  waves_n, main-loop mode}.  The 32 tile (one matrix wave) wastes less of
+// small problems on padding.
 #define LI_GROUPED_CLASSES(X)      \
-    X(0, 13, 22, 128, 32, 2, 4, 3) \
-    X(1, 16, 23, 64, 32, 2, 2, 3)  \
-    X(2, 50, 26, 32, 32, 1, 1, 3)
+    X(0, 51, 28, 128, 32, 2, 2, 9) \
+    X(1, 52, 29, 64, 32, 2, 2, 9)  \
+    X(2, 55, 27, 32, 32, 1, 1, 10) \
+    X(3, 16, 23, 64, 32, 2, 2, 3)

@@ -128,7 +128,7 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // other way, 25.7 and 23.4).  Otherwise phases, of 128 x 128 tiles
         // where the work outweighs their longer pipeline (1024 x 2048, 2.1e9
         // products: 39.1 us against 41.4 in 64 x 64; 896 x 1216, 1e9: 34.9 and 31.7).
-        if (K <= 200) return 17;
+        if (K <= 200 || (M > 704 && K <= 256)) return 17;
         if (M <= 704 && K < 700) return 27;
         return (double)M * (double)M * (double)K >= 2e9 ? 20 : 21;
     }
@@ -150,8 +150,14 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         return K >= 640 && (double)M * (double)M * (double)K >= 2.5e9 ? 15 : 14;
     }
     if (kernel == LI_KERNEL_GROUPED_GEMM || kernel == LI_KERNEL_GROUPED_COV) {
-        // the 128 class when the output has at least 256 rows and columns
-        return (M >= 256 && N >= 256) ? 0 : 1;
+        // Class 1 (64 x 64) for all but large problems: one class makes two
+        // contraction kernels, and each further one adds two that share the
+        // compute units with them badly (33 + 33 problems with sizes from 32
+        // to 1024: 74 us in class 1 alone, 130 with the class of least
+        // predicted work for each problem).  Class 0 (128 x 128)
+        // where its padding is small (24 + 24 problems from 700 to 2500:
+        // 1.49 ms, all in class 1 1.72; from 500 to 1200 0.371 and 0.382).
+        return M >= 768 && N >= 768 && K >= 256 ? 0 : 1;
     }
     if (kernel == LI_KERNEL_GEMM_LP || kernel == LI_KERNEL_GEMM_LP_SPLIT) {
         if (ceil_div(M, 256) * ceil_div(N, 256) >= cus) return kernel == LI_KERNEL_GEMM_LP ? 23 : 12;
