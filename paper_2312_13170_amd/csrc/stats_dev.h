@@ -49,15 +49,31 @@ __device__ __forceinline__ void chunk_moments(const float *col, int64_t ld, int6
     moments_finish(x0, s1, s2, (double)(r1 - r0), mean, m2);
 }
 
+// Weights of merging nb rows into na.
+__device__ __forceinline__ void merge_weights(double na, double nb, double &wm, double &wq)
+{
+    const double n = na + nb;
+    wm = nb / n;
+    wq = na * nb / n;
+}
+
+// (ma, m2a) <- merge with (mb, m2b)
+__device__ __forceinline__ void chan_merge_weighted(double &ma, double &m2a, double mb, double m2b, double wm,
+                                                    double wq)
+{
+    const double d = mb - ma;
+    ma = ma + d * wm;
+    m2a = m2a + m2b + d * d * wq;
+}
+
 // (na, ma, m2a) <- merge with (nb, mb, m2b)
 __device__ __forceinline__ void chan_merge(double &na, double &ma, double &m2a, double nb, double mb,
                                            double m2b)
 {
-    const double n = na + nb;
-    const double d = mb - ma;
-    ma = ma + d * (nb / n);
-    m2a = m2a + m2b + d * d * (na * nb / n);
-    na = n;
+    double wm, wq;
+    merge_weights(na, nb, wm, wq);
+    chan_merge_weighted(ma, m2a, mb, m2b, wm, wq);
+    na = na + nb;
 }
 
 // Merge order of the chunk partials: the chunks are split into kMergeGroups
