@@ -14,6 +14,9 @@ namespace {
 
 // ---------------------------------------------------------------- GEMM
 // C = alpha*A*B + beta*C, A M x K, B K x N, C M x N, row-major.
+// tile rows of a band in which work-groups walk the tiles (grouped_tile)
+constexpr int kGroupM = 8;
+
 template <class T>
 __global__ __launch_bounds__(T::NT) void gemm_f32_kernel(const float *__restrict__ A, int64_t lda,
                                                          const float *__restrict__ B, int64_t ldb,
@@ -46,10 +49,9 @@ int run_gemm(int64_t M, int64_t N, int64_t K, float alpha, const float *A, int64
 {
     const int tiles_m = (int)((M + T::BM - 1) / T::BM);
     const int tiles_n = (int)((N + T::BN - 1) / T::BN);
-    const int group_m = 8;
     const int nb = tiles_m * tiles_n;
     hipLaunchKernelGGL(gemm_f32_kernel<T>, dim3(nb), dim3(T::NT), 0, s, A, lda, B, ldb, C, ldc, M,
-                       N, K, alpha, beta, tiles_m, tiles_n, group_m);
+                       N, K, alpha, beta, tiles_m, tiles_n, kGroupM);
     return (int)hipGetLastError();
 }
 
@@ -87,7 +89,103 @@ int run_gemm_candidate(bool v4, int64_t M, int64_t N, int64_t K, float alpha, co
 #undef LI_RUN
 }
 
+// ------------------------------------------------------------ phased GEMM
+// The split tiles in the phases of the symmetric contractions
+// (symm_kernels.h): whole tiles as long as they fill the compute units, the
+// rest cut along K into pieces that the reduce kernel adds.
+template <class T>
+__global__ __launch_bounds__(T::NT) void gemm_phase_kernel(const float *__restrict__ A, const float *__restrict__ B,
+                                                           float *__restrict__ C, int64_t M, int64_t N, int64_t K,
+                                                           float alpha, float beta, int tiles_m, int tiles_n, int kt,
+                                                           SymPlan plan, float *__restrict__ part)
+{
+    __shared__ __attribute__((aligned(16))) float lds[T::LDS_FLOATS];
+    int b = blockIdx.x, f = 0;
+    while (b >= plan.ph[f].ntiles * plan.ph[f].chunks) {
+        b -= plan.ph[f].ntiles * plan.ph[f].chunks;
+        ++f;
+    }
+    const SymPhase ph = plan.ph[f];
+    const int u = xcd_remap(b, ph.ntiles * ph.chunks);
+    const int c = u / ph.ntiles, t = ph.tile0 + u % ph.ntiles;
+    int tm, tn;
+    grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
+    const int64_t m0 = (int64_t)tm * T::BM, n0 = (int64_t)tn * T::BN;
+    const int64_t k0 = (int64_t)kt * c / ph.chunks * T::BK, k1 = (int64_t)kt * (c + 1) / ph.chunks * T::BK;
+    f32x16 acc[T::TM][T::TN];
+    T::zero(acc);
+    T::mainloop(lds, A, K, B, N, M, N, k0, k1 < K ? k1 : K, m0, n0, acc);
+    if (ph.chunks == 1) {
+        T::store_c(lds, acc, C, N, M, N, m0, n0, alpha, beta);
+    } else if (T::active()) {
+        store_partial<T>(acc, part + (int64_t)(ph.piece0 + u) * T::BM * T::BN, threadIdx.x);
+    }
+}
+
+template <class T>
+__global__ __launch_bounds__(kReduceThreads) void gemm_phase_reduce_kernel(float *__restrict__ C, int64_t M, int64_t N,
+                                                                           float alpha, float beta, int tiles_m,
+                                                                           int tiles_n, SymPlan plan,
+                                                                           const float *__restrict__ part)
+{
+    constexpr int S = phase_blocks<T>();
+    __shared__ __attribute__((aligned(16))) float sum[kReduceThreads / 64][32 * kPhaseLd];
+    const int t = plan.split0 + blockIdx.x / S, s = blockIdx.x % S;
+    int tm, tn, br, bc;
+    grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
+    phase_block<T>(s, br, bc);
+    const int64_t r0 = (int64_t)tm * T::BM + br, c0 = (int64_t)tn * T::BN + bc;
+    if (r0 >= M || c0 >= N) return;
+    const int r = threadIdx.x / 8, c = threadIdx.x % 8 * 4;
+    float *p = C + (r0 + r) * N + c0 + c;
+    const int n = r0 + r >= M ? 0 : N - c0 - c < 4 ? (int)(N - c0 - c) : 4;  // elements of this thread
+    float old[4] = {};
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < n && beta != 0.f) old[e] = p[e];
+    phase_sum<T>(sum, part, plan, t, s);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float x = sum[0][r * kPhaseLd + c + e];
+        if (e < n) p[e] = beta != 0.f ? T::combine(alpha, x, beta, old[e]) : alpha * x;
+    }
+}
+
+template <class T>
+SymPlan gemm_phase_plan(int64_t M, int64_t N, int64_t K, double *predicted = nullptr)
+{
+    return sym_plan_for<T>((M + T::BM - 1) / T::BM * ((N + T::BN - 1) / T::BN), (K + T::BK - 1) / T::BK, 1, predicted);
+}
+
+template <class T>
+double phase_us(int64_t M, int64_t N, int64_t K)
+{
+    double us = 0.0;
+    gemm_phase_plan<T>(M, N, K, &us);
+    return us;
+}
+
+template <class T>
+int run_gemm_phases(int64_t M, int64_t N, int64_t K, float alpha, const float *A, const float *B, float beta, float *C,
+                    float *ws, hipStream_t s)
+{
+    const int tiles_m = (int)((M + T::BM - 1) / T::BM), tiles_n = (int)((N + T::BN - 1) / T::BN);
+    const int nb = tiles_m * tiles_n, kt = (int)((K + T::BK - 1) / T::BK);
+    const SymPlan plan = gemm_phase_plan<T>(M, N, K);
+    hipLaunchKernelGGL(gemm_phase_kernel<T>, dim3((unsigned)plan.units), dim3(T::NT), 0, s, A, B, C, M, N, K, alpha,
+                       beta, tiles_m, tiles_n, kt, plan, ws);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || plan.pieces == 0) return (int)e;
+    hipLaunchKernelGGL(gemm_phase_reduce_kernel<T>, dim3((unsigned)((nb - plan.split0) * phase_blocks<T>())),
+                       dim3(kReduceThreads), 0, s, C, M, N, alpha, beta, tiles_m, tiles_n, plan, (const float *)ws);
+    return (int)hipGetLastError();
+}
+
+using PhaseTile128 = SplitTile<128, 128, 32, 2, 2, 4, true, false, false>;
+using PhaseTile64 = SplitTile<64, 64, 32, 2, 2, 4, true, false, false>;
+
 // ---------------------------------------------------------- stream-K GEMM
+// (for rows too long for the split tiles' offsets, on the FP32 cores)
 // The nb output tiles times kt K-tiles form one iteration space split
 // evenly over the G work-groups (the schedule of the symmetric
 // contractions, symm_kernels.h): a range covers whole tiles, stored with
@@ -175,8 +273,8 @@ struct SkPlan {
     int tiles_n, nb, kt, G;
 };
 
-// Whether and how the stream-K schedule runs M x N x K: with at least 32
-// K-tiles per output tile, when the tiles number fewer than the compute
+// Whether and how the stream-K schedule (or its place in phases) runs M x N x
+// K: with at least 32 K-tiles per output tile, when the tiles number fewer than the compute
 // units or their last wave fills at most 60% of them (and there are fewer
 // than four waves, beyond which that tail matters little).
 bool gemm_streamk_plan(int64_t M, int64_t N, int64_t K, SkPlan &p)
@@ -246,6 +344,26 @@ int launch_gemm_f32_streamk(int64_t M, int64_t N, int64_t K, float alpha, const 
     SkPlan p;
     if (!gemm_streamk_plan(M, N, K, p) || !ws) return (int)hipErrorInvalidValue;
     hipStream_t s = (hipStream_t)stream;
+    if (K <= kSplitMaxLd && N <= kSplitMaxLd) {
+        // The least predicted time of the plain schedule and of phases of 128
+        // x 128 and of 64 x 64 tiles, whose plans' own prediction is scaled to
+        // these kernels (measured, us, plain / 128 / 64: 1024 x 1024 x 4096
+        // 70.6 / 57.1 / 72.3; 300 x 200 x 4100 33.2 / 21.0 / 15.3; 512 x 512 x
+        // 65536 480 / 170 / 235; 1000 x 1500 x 3000 69.8 / 73.2 / 83.2; 3000^3
+        // 345 / 293 / 373.  Stream-K on the FP32 cores: 87.5, 47.1, 274, 94.5,
+        // 466).
+        const double plain = split_gemm_us(M, N, K);
+        const double t128 = 1.18 * phase_us<PhaseTile128>(M, N, K) + 5.0;
+        const double t64 = 1.02 * phase_us<PhaseTile64>(M, N, K) + 6.0;
+        // Few tiles: always cut, as stream-K did (it summed a small output in
+        // up to 256 ranges, 330 x 448 x 1472 with an rms error of 1.8e-7;
+        // uncut, the split tiles' is 2.1e-7).
+        const bool few = p.nb < 32;
+        if ((few || t128 < plain) && t128 <= t64)
+            return run_gemm_phases<PhaseTile128>(M, N, K, alpha, A, B, beta, C, ws, s);
+        if (few || t64 < plain) return run_gemm_phases<PhaseTile64>(M, N, K, alpha, A, B, beta, C, ws, s);
+        return launch_gemm_f32(tune_pick(LI_KERNEL_GEMM_F32, M, N, K), M, N, K, alpha, A, K, B, N, beta, C, N, stream);
+    }
     const bool v4 = K % 4 == 0 && N % 4 == 0 && aligned16(A) && aligned16(B);
     return v4 ? run_gemm_streamk<SkTileVec>(p, M, N, K, alpha, A, B, beta, C, ws, s)
               : run_gemm_streamk<SkTileScalar>(p, M, N, K, alpha, A, B, beta, C, ws, s);

@@ -48,6 +48,7 @@ const TileCfg &tune_cfg(int kernel, int idx);
 // table slot of a call
 int tune_key(int kernel, int64_t M, int64_t N, int64_t K);
 // candidate index for a problem: forced > table > built-in heuristic
+double split_gemm_us(int64_t M, int64_t N, int64_t K);  // predicted time of the FP32 product's split tiles
 int tune_pick(int kernel, int64_t M, int64_t N, int64_t K);
 
 // ---------------------------------------------------------------- launchers

@@ -470,27 +470,21 @@ __global__ __launch_bounds__(T::NT) void sym_phase_kernel(SymArgs a, float *__re
     }
 }
 
-// Adds the pieces of a cut tile, one work-group per 32 x 32 block: each wave
-// sums every fourth chunk, the four sums meet in LDS (a fixed order).  Bound
-// by reading the pieces; with one wave per block, all its chunks in turn, too
-// few loads were in flight (correlation 501 x 20011, 25 chunks of 10 tiles:
-// 17.9 us, now 6.2; covariance 2048 x 4096: 13.0, now 10.9).
+// The sum of the pieces of cut tile t over one of its 32 x 32 blocks, in LDS
+// (sum[0], [32][33]), by a work-group of kReduceThreads: each wave sums every
+// fourth chunk, the four sums meet in LDS (a fixed order).  Bound by reading
+// the pieces; with one wave per block, all its chunks in turn, too few loads
+// were in flight (correlation 501 x 20011, 25 chunks of 10 tiles: 17.9 us,
+// now 6.2; covariance 2048 x 4096: 13.0, now 10.9).
+constexpr int kPhaseLd = 33;
 template <class T>
-__global__ __launch_bounds__(kReduceThreads) void sym_phase_reduce_kernel(SymArgs a, const float *__restrict__ part,
-                                                                          int tiles, SymPlan plan)
+__device__ __forceinline__ void phase_sum(float (&sum)[kReduceThreads / 64][32 * kPhaseLd],
+                                          const float *__restrict__ part, const SymPlan &plan, int t, int s)
 {
-    constexpr int S = phase_blocks<T>(), B = T::TM * T::TN, W = kReduceThreads / 64, LD = 33;
-    __shared__ __attribute__((aligned(16))) float sum[W][32 * LD];
-    __shared__ double shift[64];
-    const int t = plan.split0 + blockIdx.x / S, s = blockIdx.x % S;
+    constexpr int B = T::TM * T::TN, W = kReduceThreads / 64;
     const int w = s / B, i = s % B / T::TN, j = s % T::TN;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (w / T::WN) * (T::BM / T::WM), wn0 = (w % T::WN) * (T::BN / T::WN);
-    const int br = wm0 + 32 * i, bc = wn0 + 32 * j;
-    int tm, tn;
-    upper_tile(t, tiles, tm, tn);
-    const int64_t r0 = (int64_t)tm * T::BM + br, c0 = (int64_t)tn * T::BN + bc;
-    if (r0 > c0 || c0 >= a.n) return;  // (below the diagonal: the mirrored block's)
     SymPhase ph = plan.ph[plan.n - 1];
     if (t < ph.tile0) ph = plan.ph[plan.n - 2];
     f32x16 acc = {};
@@ -500,19 +494,47 @@ __global__ __launch_bounds__(kReduceThreads) void sym_phase_reduce_kernel(SymArg
         add_partial_block<T>(acc, i, j, p + (int64_t)c * ph.ntiles * T::BM * T::BN, w * 64 + lane);
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-        sum[wave][(T::acc_row(wm0, i, v, lane) - br) * LD + T::acc_col(wn0, j, lane) - bc] = acc[v];
-    if constexpr (T::XFORM != 0) {
-        if (wave == 0) shift[lane] = fused_shift<T>(a, lane < 32 ? r0 + lane : c0 + lane - 32);
-    }
+        sum[wave][(T::acc_row(wm0, i, v, lane) - wm0 - 32 * i) * kPhaseLd + T::acc_col(wn0, j, lane) - wn0 - 32 * j] =
+            acc[v];
     __syncthreads();
-    for (int x = threadIdx.x; x < 32 * LD; x += kReduceThreads) {
+    for (int x = threadIdx.x; x < 32 * kPhaseLd; x += kReduceThreads) {
         float y = sum[0][x];
 #pragma unroll
         for (int q = 1; q < W; ++q) y += sum[q][x];
         sum[0][x] = y;
     }
     __syncthreads();
-    write_sym<T, 32, 32, LD, kReduceThreads>(sum[0], shift, threadIdx.x, a, r0, c0);
+}
+
+// first row and column of block s of a tile of type T
+template <class T>
+__device__ __forceinline__ void phase_block(int s, int &br, int &bc)
+{
+    constexpr int B = T::TM * T::TN;
+    const int w = s / B;
+    br = (w / T::WN) * (T::BM / T::WM) + s % B / T::TN * 32;
+    bc = (w % T::WN) * (T::BN / T::WN) + s % T::TN * 32;
+}
+
+template <class T>
+__global__ __launch_bounds__(kReduceThreads) void sym_phase_reduce_kernel(SymArgs a, const float *__restrict__ part,
+                                                                          int tiles, SymPlan plan)
+{
+    constexpr int S = phase_blocks<T>();
+    __shared__ __attribute__((aligned(16))) float sum[kReduceThreads / 64][32 * kPhaseLd];
+    __shared__ double shift[64];
+    const int t = plan.split0 + blockIdx.x / S, s = blockIdx.x % S;
+    int tm, tn, br, bc;
+    upper_tile(t, tiles, tm, tn);
+    phase_block<T>(s, br, bc);
+    const int64_t r0 = (int64_t)tm * T::BM + br, c0 = (int64_t)tn * T::BN + bc;
+    if (r0 > c0 || c0 >= a.n) return;  // (below the diagonal: the mirrored block's)
+    if constexpr (T::XFORM != 0) {
+        const int l = threadIdx.x;
+        if (l < 64) shift[l] = fused_shift<T>(a, l < 32 ? r0 + l : c0 + l - 32);
+    }
+    phase_sum<T>(sum, part, plan, t, s);
+    write_sym<T, 32, 32, kPhaseLd, kReduceThreads>(sum[0], shift, threadIdx.x, a, r0, c0);
 }
 
 // The plan for nb tiles of kt K-tiles on W work-groups.  Predicted time: a
@@ -521,7 +543,8 @@ __global__ __launch_bounds__(kReduceThreads) void sym_phase_reduce_kernel(SymArg
 // `piece` per piece.  Chunks are at least eight K-tiles long: shorter ones
 // only add pieces (one 64 x 64 tile, 11776 samples: 256 chunks 0.21 ms, 46
 // chunks 0.035 ms).
-inline SymPlan sym_plan(int64_t nb, int64_t kt, int64_t W, double us, double fill, double piece)
+inline SymPlan sym_plan(int64_t nb, int64_t kt, int64_t W, double us, double fill, double piece,
+                        double *predicted = nullptr)
 {
     SymPlan best{};
     double tbest = 0;
@@ -562,6 +585,7 @@ inline SymPlan sym_plan(int64_t nb, int64_t kt, int64_t W, double us, double fil
         }
     }
     for (int f = 0; f < best.n; ++f) best.units += best.ph[f].ntiles * best.ph[f].chunks;
+    if (predicted) *predicted = tbest;
     return best;
 }
 
@@ -569,13 +593,13 @@ inline SymPlan sym_plan(int64_t nb, int64_t kt, int64_t W, double us, double fil
 // pieces for each).  The 64 x 64 tile gains 13% from a second work-group on a
 // compute unit where the chunks are long.
 template <class T>
-SymPlan sym_plan_for(int64_t nb, int64_t kt, int passes)
+SymPlan sym_plan_for(int64_t nb, int64_t kt, int passes, double *predicted = nullptr)
 {
     const int64_t cus = device_cu_count();
     const bool big = T::BM >= 128;
     const int64_t W = !big && nb * kt >= cus * 2 * 32 ? 2 * cus : cus;
     return sym_plan(nb, kt, W < kStreamMaxGroups ? W : kStreamMaxGroups, (big ? 1.05 : W > cus ? 0.84 : 0.45) * passes,
-                    big ? 4.0 : 2.0, big ? 0.02 : 0.005);
+                    big ? 4.0 : 2.0, big ? 0.02 : 0.005, predicted);
 }
 
 // Bytes of split-K partials a candidate list may need for order n.

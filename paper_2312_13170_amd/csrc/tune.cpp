@@ -82,7 +82,7 @@ const SplitCost kSplitF32[] = {
     {55, 5.02, 0.41, 0.0102, 0.0055},  // 32 x 32, K-tile 32
 };
 
-int split_pick(int64_t M, int64_t N, int64_t K)
+int split_pick(int64_t M, int64_t N, int64_t K, double *predicted = nullptr)
 {
     int best = kSplitF32[0].idx;
     double tbest = HUGE_VAL;
@@ -96,6 +96,7 @@ int split_pick(int64_t M, int64_t N, int64_t K)
             best = c.idx;
         }
     }
+    if (predicted) *predicted = tbest;
     return best;
 }
 
@@ -168,6 +169,13 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
 }
 
 }  // namespace
+
+double split_gemm_us(int64_t M, int64_t N, int64_t K)
+{
+    double us = 0.0;
+    split_pick(M, N, K, &us);
+    return us;
+}
 
 int tune_num(int kernel)
 {
