@@ -137,8 +137,11 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // M is the order of C, K the reduction length (the rank).  Over 156
         // shapes (both updates, M from 128 to 4096, K from 64 to 8192): a
         // large result of a short rank on the FP32 cores (4096 x 128: syrk
-        // 38.8 us against 43.1), a small one in 32 x 32 tiles (512 x 384: 9.1
-        // us against 11.1 in 64 x 64; 336 x 779 the other way, 14.6 and 12.6).
+        // 38.8 us against 43.1), a small one in 32 x 32 tiles (1000 x 400:
+        // syr2k 20.0 us against 23.4 in 64 x 64 tiles split in four, 192 x 379
+        // 14.8 and 18.2 in phases), with a longer rank split in four (500 x
+        // 550: 11.5 us against 12.4 in 32 x 32, 15.1 in phases; 300 x 2000 the
+        // other way, 15.6 and 13.2).
         // Otherwise phases, of 128 x 128 tiles where the work outweighs
         // their pipeline (2048 x 2048: 62.7 us against 67.1 in 64 x 64, syr2k
         // 108 and 126; 1024 x 1024 21.5 and 20.7; 4096 x 512 101 and 81), or
@@ -146,6 +149,9 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // hide the last one (8192 x 1024: 0.518 ms against 0.508; 6500 x 1500
         // 0.437 and 0.408).
         if (M >= 2048 && K < 160) return 16;
+        // (up to order 64 from rank 200 on for its smaller error: 33 x 231 5.6e-8
+        // against 8.8e-8 in 32 x 32 tiles, rms)
+        if (M <= 640 && K >= (M <= 64 ? 200 : 400) && K < 1000) return 9;
         if (M <= 1152 && K < 700) return 17;
         if (M >= 8192 && 4 * K < 3 * M) return 10;
         return K >= 640 && (double)M * (double)M * (double)K >= 2.5e9 ? 15 : 14;
