@@ -4,13 +4,15 @@
 Headline workload: the FP32 two-GEMM chain D = alpha*(A*B)*C + beta*D with
 NI = NJ = NK = NL = 2048 (tmp kept in HBM), inputs uniform in [-1, 1) from
 seed 2, alpha = 1.5, beta = 1.2.  One step is one li_mm2 call (two FP32
-matrix-core GEMM launches).  W untimed warm-up steps, then K timed steps
+GEMM launches on the matrix cores).  W untimed warm-up steps, then K timed steps
 between HIP events on the stream the kernels run on; inputs are resident in
 HBM before timing starts.
 
 Printed: one JSON line with the contract fields, plus
   roofline      the dominant kernel (the FP32 GEMM launch of the step) against
-                the FP32 matrix peak: its flops over its own mean duration,
+                the peak of its FP32 products (six bf16 matrix products for
+                each, a sixth of the dense bf16 peak): its flops over its own
+                mean duration,
                 K launches of each of the step's two products timed back to
                 back between HIP events on their stream,
   step          the whole step's rate against the same peak (launch gaps
@@ -48,8 +50,11 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_FP32_MFMA = 157.3   # TFLOP/s, MI355X dense FP32 matrix
 PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense bf16/fp16 matrix
+# The FP32 products run on the bf16 matrix cores: each operand is split exactly
+# into three bf16 parts and six of the nine part products are summed (the FP32
+# matrix cores' own dense peak is 157.3).
+PEAK_FP32_SPLIT = PEAK_BF16_MFMA / 6
 PEAK_HBM = 8000.0        # GB/s
 
 ROWS_DEFAULT = "gemm256,cov,corr,precision,grouped,forms,paper1024,rank,matvec,vendor"
@@ -306,15 +311,18 @@ def main():
                    "settle": "%d untimed steps (%.0f ms) before the %d warm-up steps" % (
                        settle_steps, args.settle_ms, args.warmup)},
         "roofline": {"bound": "mfma", "kernel": "gemm_f32_kernel 2048x2048x2048 (both launches of the step)",
-                     "achieved": round(achieved, 2), "peak": PEAK_FP32_MFMA, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP32_MFMA, 4), "traffic": committed_traffic(),
+                     "achieved": round(achieved, 2), "peak": round(PEAK_FP32_SPLIT, 1), "unit": "TFLOP/s",
+                     "frac": round(achieved / PEAK_FP32_SPLIT, 4),
+                     "peak_note": "dense bf16 matrix peak / 6: an FP32 product is six bf16 products of operands "
+                                  "split exactly into three bf16 parts, summed in FP32",
+                     "traffic": committed_traffic(),
                      "launch_us_mean": round(launch_ms * 1e3, 2),
                      "launch_us_first_product": round(d1 * 1e3, 2),
                      "launch_us_second_product": round(d2 * 1e3, 2),
                      "launch_us_first_product_events_each": round(each_ms * 1e3, 2)},
         "step": {"ms_mean": round(ms_step, 4),
                  "TFLOP/s": round(value / 1e3, 2),
-                 "frac_fp32_mfma": round(value / 1e3 / PEAK_FP32_MFMA, 4)},
+                 "frac_fp32_split": round(value / 1e3 / PEAK_FP32_SPLIT, 4)},
     }
     if per_step:
         out["step"].update({"ms_median": round(per_step[len(per_step) // 2], 4),
@@ -611,7 +619,7 @@ def measure_stats(want, torch, li, synth, timer, reps, rows, checks):
         ms_cold = timer.time_cold(fn, 10, flush)
         del flush
         rows[kind + "_4096x2048"] = dict(st, **{"GFLOP/s": round(f / ms / 1e6, 1),
-                                               "frac_fp32_mfma": round(f / ms / 1e9 / PEAK_FP32_MFMA, 4),
+                                               "frac_fp32_split": round(f / ms / 1e9 / PEAK_FP32_SPLIT, 4),
                                                "ms_cold_cache": round(ms_cold, 4)})
         fn()
         torch.cuda.synchronize()
@@ -659,7 +667,7 @@ def measure_precision(torch, li, synth, timer, rows, checks):
     for prec in ("fp32", "bf16", "fp16", "bf16x3"):
         fn = lambda: li.li_gemm_ex(M, N, K, 1.0, A, B, 0.0, C, prec, ws)
         ms = timer.time(fn, 10, 1)
-        peak = PEAK_FP32_MFMA if prec == "fp32" else PEAK_BF16_MFMA
+        peak = PEAK_FP32_SPLIT if prec == "fp32" else PEAK_BF16_MFMA
         rows["gemm_8192_" + prec] = {"ms": round(ms, 3), "TFLOP/s": round(f / ms / 1e9, 1),
                                      "frac_peak": round(f / ms / 1e9 / peak, 4)}
         outs[prec] = C.cpu().numpy()[sample]
@@ -722,7 +730,7 @@ def measure_rank(torch, li, synth, timer, reps, rows, checks):
         ms = timer.time(lambda: li.li_mm3(n, n, n, n, n, dA, dB, dC, dD, E, F, G), reps, 1)
         f = 3 * 2.0 * n ** 3
         rows["mm3_%d" % n] = {"ms": round(ms, 4), "GFLOP/s": round(f / ms / 1e6, 1),
-                              "frac_fp32_mfma": round(f / ms / 1e9 / PEAK_FP32_MFMA, 4)}
+                              "frac_fp32_split": round(f / ms / 1e9 / PEAK_FP32_SPLIT, 4)}
         sample = np.arange(0, n, 8)
         G_out = G.cpu().numpy()[sample]
         r = synth.rank_update_inputs(n, n, seed=7)
@@ -735,14 +743,14 @@ def measure_rank(torch, li, synth, timer, reps, rows, checks):
         f1 = float(n) * (n + 1) * n + 3.0 * n * n
         ms = timer.time(lambda: li.li_syrk(n, n, 1.5, A, 1.2, C, ws), reps, 1)
         rows["syrk_%d" % n] = {"ms": round(ms, 4), "GFLOP/s": round(f1 / ms / 1e6, 1),
-                               "frac_fp32_mfma": round(f1 / ms / 1e9 / PEAK_FP32_MFMA, 4)}
+                               "frac_fp32_split": round(f1 / ms / 1e9 / PEAK_FP32_SPLIT, 4)}
         C.copy_(C0)
         li.li_syrk(n, n, 1.5, A, 1.2, C, ws)
         syrk_out = C.cpu().numpy()[sample]
         f2 = 2.0 * n * (n + 1) * n + 4.0 * n * n
         ms = timer.time(lambda: li.li_syr2k(n, n, 1.5, A, B, 1.2, C, ws), reps, 1)
         rows["syr2k_%d" % n] = {"ms": round(ms, 4), "GFLOP/s": round(f2 / ms / 1e6, 1),
-                                "frac_fp32_mfma": round(f2 / ms / 1e9 / PEAK_FP32_MFMA, 4)}
+                                "frac_fp32_split": round(f2 / ms / 1e9 / PEAK_FP32_SPLIT, 4)}
         C.copy_(C0)
         li.li_syr2k(n, n, 1.5, A, B, 1.2, C, ws)
         syr2k_out = C.cpu().numpy()[sample]

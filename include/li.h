@@ -100,10 +100,9 @@ li_status li_gemm(int64_t M, int64_t N, int64_t K, float alpha, const float *A,
  * For LI_FP32 the workspace may be NULL (the li_gemm schedule); with one of
  * li_gemm_ex_workspace_bytes bytes, shapes whose output tiles would leave
  * compute units idle (fewer 128 x 128 tiles than compute units, or a last
- * wave of tiles filling at most 60% of them, with K >= 1024) run a
- * stream-K schedule: the (tile, K-tile) iterations split evenly over the
- * compute units, pieces of shared tiles added in a fixed order (results
- * are deterministic); li_gemm_ex_workspace_bytes is 0 for other shapes.
+ * wave of tiles filling at most 60% of them, with K >= 1024) may have
+ * tiles cut along K, their pieces added in a fixed order (results are
+ * deterministic); li_gemm_ex_workspace_bytes is 0 for other shapes.
  * LI_FP16 turns magnitudes beyond 65504 into infinities, as the format
  * does. */
 size_t li_gemm_ex_workspace_bytes(int64_t M, int64_t N, int64_t K, li_precision p);
@@ -332,8 +331,9 @@ enum {
 typedef struct li_tile_config {
     int32_t bm, bn, bk;     /* block tile and K-tile                    */
     int32_t waves_m, waves_n;
-    int32_t split_k;        /* reduction split (1 = none; 0 = stream-K:
-                               balanced ranges of (tile, K-tile) work)  */
+    int32_t split_k;        /* reduction split (1 = none; 0 = balanced:
+                               stream-K ranges of (tile, K-tile) work,
+                               modes 9 to 11 phases of cut tiles)       */
     int32_t prefetch;       /* main-loop mode 1-4 (1, 2: K-tiles in flight
                                from HBM; 3: 2 plus operand reads pipelined
                                across the barrier; 4: direct HBM-to-LDS

@@ -25,7 +25,7 @@ import os
 import sqlite3
 
 PKG = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ["csrc/f32_tile.h", "csrc/gemm_f32.hip", "csrc/tiles.h", "csrc/stats.hip",
+KERNEL_SOURCES = ["csrc/f32_tile.h", "csrc/split_tile.h", "csrc/gemm_f32.hip", "csrc/tiles.h", "csrc/stats.hip",
                   "csrc/stats_dev.h", "csrc/gemm_lp.hip", "csrc/grouped.hip", "csrc/symm_kernels.h",
                   "csrc/symm_rows.hip", "csrc/matvec.hip", "csrc/cov_fused.hip", "tune_gfx950.txt"]
 
