@@ -48,6 +48,10 @@ const TileCfg &tune_cfg(int kernel, int idx);
 // table slot of a call
 int tune_key(int kernel, int64_t M, int64_t N, int64_t K);
 // candidate index for a problem: forced > table > built-in heuristic
+// Longest rows (elements) of a split tile's operand: offsets inside a block
+// tile are 32-bit byte offsets (256 rows, or 64 k values, of this many
+// elements).
+constexpr int64_t kSplitMaxLd = (int64_t)1 << 21;
 double split_gemm_us(int64_t M, int64_t N, int64_t K);  // predicted time of the FP32 product's split tiles
 int tune_pick(int kernel, int64_t M, int64_t N, int64_t K);
 

@@ -62,6 +62,7 @@
 #pragma once
 
 #include "f32_tile.h"
+#include "li_internal.h"
 
 namespace li {
 
@@ -90,10 +91,6 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t &p0, uint3
     p2 = __builtin_amdgcn_perm(v, u, kPack);
     lost |= u | v;
 }
-
-// Longest rows (elements) of an operand: offsets inside a block tile are 32-bit
-// byte offsets (256 rows, or 64 k values, of this many elements).
-constexpr int64_t kSplitMaxLd = (int64_t)1 << 21;
 
 // Splitting waves of the main-loop modes 9 to 11 of the candidate lists.
 constexpr int split_waves(int mode) { return mode == 10 ? 2 : mode == 11 ? 8 : 4; }

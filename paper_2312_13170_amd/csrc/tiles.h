@@ -5,12 +5,12 @@
 
 // {index, bm, bn, bk, waves_m, waves_n, split_k, prefetch depth}
 // split_k: 1 none, > 1 split reduction into that many chunks, 0 stream-K or,
-// for the split tiles, a plan of phases (symmetric contractions only).  prefetch: main-loop mode 1-4; in the FP32
-// GEMM list 5-7 are modes 1-3 with B transposed into LDS and 8 is the
-// direct-to-LDS loop with a two-stage ring (K a multiple of the K-tile).
-// 9, 10, 11: operands split into three bf16 parts, multiplied on the bf16
-// matrix cores (split_tile.h), with 4, 2 and 8 splitting waves beside the
-// waves_m x waves_n matrix waves.
+// for the split tiles, a plan of phases (symmetric contractions only).
+// prefetch: main-loop mode 1-4; in the FP32 GEMM list 5-7 are modes 1-3 with
+// B transposed into LDS and 8 is the direct-to-LDS loop with a two-stage ring
+// (K a multiple of the K-tile).  9, 10, 11: operands split into three bf16
+// parts, multiplied on the bf16 matrix cores (split_tile.h), with 4, 2 and 8
+// splitting waves beside the waves_m x waves_n matrix waves.
 #define LI_GEMM_F32_CANDIDATES(X)            \
     X(0, 128, 128, 32, 2, 2, 1, 1)           \
     X(1, 128, 128, 16, 2, 2, 1, 1)           \

@@ -113,8 +113,9 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
 {
     const int64_t cus = 256;  // compute units of an MI355X
     if (kernel == LI_KERNEL_GEMM_F32) {
-        if (K >= kSplitMinK) return split_pick(M, N, K);
-        // by the bit length of the output's side, as searched
+        if (K >= kSplitMinK && K <= kSplitMaxLd && N <= kSplitMaxLd) return split_pick(M, N, K);
+        // (short reductions, rows too long for the split tiles) by the bit
+        // length of the output's side, as searched
         const int side = tune_key(kernel, M, N, K);
         return side <= 8 ? 2 : side <= 11 ? 20 : side == 12 ? 44 : 49;
     }
