@@ -5,7 +5,10 @@ For each family and table slot, every compiled candidate is forced in turn
 (li_tune_force) and the ordinary entry point is timed with HIP events on
 the current stream (1 warm-up, then the mean of `reps` calls); the fastest
 candidate is written to the table (li_tune_set) and the table is saved as
-text (li_tune_save), which li.py loads at import.
+text (li_tune_save), which li.py loads at import.  The table that comes with
+the library has entries for the 16-bit products only: the FP32 products, the
+symmetric contractions and the batches go by the measured rules of
+csrc/tune.cpp, which searched entries would override.
 
 Representative problems per table slot (li_tune_key:
 the GEMM families key by the output's area, which for the square problems

@@ -5,7 +5,8 @@
 // matrix never goes through HBM.  Each element is loaded by every tile of
 // its block row and column, so the transform is repeated that many times
 // and has to be cheap: one FP32 subtraction of the mean rounded to FP32
-// (and one product for correlation), applied on the way into LDS by the
+// (and one product for correlation), applied by the splitting waves of the split
+// tiles before the split (SplitLoader::store), on the way into LDS by the
 // register-staged loops (F32Tile::store_centred) and after the LDS reads by
 // the direct-to-LDS loop (F32Tile::xform_frag); see F32Tile::XRegs.
 // The statistics themselves (mean, stddev) are those of the FP64 kernels.

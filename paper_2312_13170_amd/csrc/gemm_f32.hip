@@ -1,6 +1,6 @@
 // FP32 GEMM and the column-form symmetric contraction (matrix cores,
-// loop-internalised reduction; see f32_tile.h for the tiling and
-// symm_kernels.h for the symmetric kernels).
+// loop-internalised reduction; see split_tile.h and f32_tile.h for the tiling
+// and symm_kernels.h for the symmetric kernels and the phases).
 #include <hip/hip_runtime.h>
 
 #include "f32_tile.h"

@@ -1,7 +1,8 @@
-// Symmetric contractions on the FP32 matrix-core tile (f32_tile.h).
+// Symmetric contractions on the split tile (split_tile.h, bf16 matrix cores) and
+// the FP32 matrix-core tile (f32_tile.h).
 //
 // Only block tiles with tile column >= tile row are computed; the epilogue
-// writes each value to (r, c) and (c, r) from the same register.  Three
+// writes each value to (r, c) and (c, r).  Three
 // operand forms share the kernels:
 //   kSymCols : S = Y^T Y, Y (kdim x n) row-major; both operands k-major
 //              (covariance / correlation after centring; T has A_KMAJOR).

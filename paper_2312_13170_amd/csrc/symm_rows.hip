@@ -1,4 +1,4 @@
-// Row-form symmetric rank updates on the FP32 matrix cores:
+// Row-form symmetric rank updates on the matrix cores:
 //   syrk : C = alpha * A A^T + beta * C
 //   syr2k: C = alpha * (A B^T + B A^T) + beta * C
 // A, B are n x k row-major, C is n x n (whole matrix).  The product is
