@@ -85,9 +85,12 @@ li_status li_init(void);
  * A: M x K, B: K x N, C: M x N, FP32 device pointers.  C must not overlap A
  * or B.  FP32 products with FP32 accumulation: on the FP32 matrix cores, or
  * (main-loop modes 9 to 11 below) on the bf16 matrix cores from operands
- * split exactly into three bf16 parts, whose result is at least as close to
- * the exact one; infinities, NaN, subnormal and other values that the parts
- * cannot hold give what the FP32 cores give. */
+ * split exactly into three bf16 parts.  The split sums are about three times
+ * closer to the exact ones (rms, dense operands); a result of a single
+ * non-zero product, as with a diagonal operand, is off by at most one unit in
+ * its last place, where the FP32 cores round to half of one.  Infinities,
+ * NaN, subnormal and other values that the parts cannot hold give what the
+ * FP32 cores give. */
 li_status li_gemm(int64_t M, int64_t N, int64_t K, float alpha, const float *A,
                   const float *B, float beta, float *C, li_stream stream);
 

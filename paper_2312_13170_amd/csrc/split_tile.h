@@ -1,20 +1,26 @@
 // FP32 block tile on the bf16 matrix cores: every operand element is split
 // exactly into three bf16 parts and six of the nine part products are summed.
 //
-//   x = x0 + x1 + x2,  x0 = x cut to bf16, x1 = bf16(x - x0), x2 = x - x0 - x1
+//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1
 //
+// (to nearest even; Henry, Tang and Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations", 2019).
 // Both subtractions are exact, and 3 x 8 significant bits hold the 24 of an
-// FP32 value, so the parts are the value; only the middle one is rounded (to
-// nearest even), which leaves a third part of either sign.  The products
-// x2*y1, x1*y2 and x2*y2, together below 3 * 2^-25 of x*y and of either sign,
-// are left out; the other six are exact in the matrix cores' FP32 sums.  The
-// leading products x0*y0 go to one accumulator and the other five to a
-// second one, whose sums are 2^-7 of the first's, so that the roundings that
-// count are those of the leading sum alone.  The FP32 cores round every
-// product and every two-wide sum; against 64 bits the split is 3 times
-// closer (rms relative to the result's, U[-1, 1), K = 256 / 2048 / 8192:
-// 9.1e-8 / 2.5e-7 / 5.5e-7, FP32 cores 2.9e-7 / 8.1e-7 / 1.6e-6; one
-// accumulator for all six products 2.5e-7 / 7.0e-7 / 1.45e-6).
+// FP32 value, so the parts are the value.  A rounded first part leaves at
+// most 2^-8 of x's power of two to the second and 2^-17 to the third, so the
+// products x2*y1, x1*y2 and x2*y2, which are left out, are together below
+// (2 + 2^-8) * 2^-25 of x*y, of either sign (rms 0.18 * 2^-25; with the first
+// part cut instead up to 7.9 * 2^-25, rms 0.71); the other six are exact in
+// the matrix cores' FP32 sums.  A result of a single product is then off by
+// up to one unit in the last place, half of it the omission's (rms 2.6e-8 of
+// it, 2.5e-8 where the product is rounded alone).  The leading products
+// x0*y0 go to one accumulator and the other five to a second one, whose sums
+// are 2^-7 of the first's, so that the roundings that count are those of the
+// leading sum alone.  The FP32 cores round every product and every two-wide
+// sum; against 64 bits the split is 3 times closer (rms relative to the
+// result's, U[-1, 1), K = 256 / 2048 / 8192: 9.1e-8 / 2.5e-7 / 5.5e-7, FP32
+// cores 2.9e-7 / 8.1e-7 / 1.6e-6; one accumulator for all six products
+// 2.5e-7 / 7.0e-7 / 1.45e-6).
 //
 // Why: six bf16 products still run 2.6 times as fast as one on the FP32
 // cores (2.5 PFLOP/s / 6 against 157 TFLOP/s).  Measured (li_gemm, beta != 0,
@@ -25,8 +31,8 @@
 //
 // Elements that the three parts cannot hold are noticed: a third part with
 // bits below bf16's (magnitudes of about 2^-110 and less) while splitting,
-// infinities and NaN, and sums that left the finite range, by the NaN or
-// infinity they leave in the block tile.  The block tile is then reduced
+// infinities and NaN, values that round to infinity as bf16, and sums that
+// left the finite range, by the NaN or infinity they leave in the block tile.  The block tile is then reduced
 // again on the FP32 cores, so every input gives what they give.
 //
 // Work split.  Splitting is paid once per element and block tile: PW
@@ -81,13 +87,12 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t &p0, uint3
     // than x)
 #pragma clang fp contract(off)
     constexpr uint32_t kHigh = 0xffff0000u, kPack = 0x07060302u;  // high halves of two words
-    uint32_t u = __builtin_bit_cast(uint32_t, x), v = __builtin_bit_cast(uint32_t, y);
-    p0 = __builtin_amdgcn_perm(v, u, kPack);
-    x -= __builtin_bit_cast(float, u & kHigh);
-    y -= __builtin_bit_cast(float, v & kHigh);
+    p0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2_t));
+    x -= __builtin_bit_cast(float, p0 << 16);
+    y -= __builtin_bit_cast(float, p0 & kHigh);
     p1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2_t));
-    u = __builtin_bit_cast(uint32_t, x - __builtin_bit_cast(float, p1 << 16));
-    v = __builtin_bit_cast(uint32_t, y - __builtin_bit_cast(float, p1 & kHigh));
+    const uint32_t u = __builtin_bit_cast(uint32_t, x - __builtin_bit_cast(float, p1 << 16));
+    const uint32_t v = __builtin_bit_cast(uint32_t, y - __builtin_bit_cast(float, p1 & kHigh));
     p2 = __builtin_amdgcn_perm(v, u, kPack);
     lost |= u | v;
 }

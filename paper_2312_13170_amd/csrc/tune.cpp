@@ -106,6 +106,17 @@ int split_pick(int64_t M, int64_t N, int64_t K, double *predicted = nullptr)
 // x 126: 10.6 against 9.4, from K = 120 never behind by more than 3%).
 constexpr int64_t kSplitMinK = 120;
 
+// Results of fewer products than this stay on the FP32 cores wherever the
+// split tiles would be taken, for their smaller error: the part products that
+// the split leaves out reach half a unit in the last place of a product, which
+// the shorter chain of roundings makes up for from two products on in the rms
+// and from three on at worst (order 700, U[-1, 1), error over the sum of
+// magnitudes, FP32 cores and split, rms and worst: K = 1 2.53e-8 and 2.58e-8,
+// 6.0e-8 and 9.0e-8; K = 2 2.53e-8 and 2.14e-8, 1.1e-7 and 1.2e-7; K = 3
+// 2.50e-8 and 1.84e-8, 1.5e-7 and 1.1e-7).  Both take 7.3 us there, a batch of
+// 64 products of K = 4 23 us.
+constexpr int64_t kSplitMinSum = 4;
+
 // Built-in choice for slots the table does not hold: for the FP32 products
 // the split tiles, and with a short reduction one of the shapes the search
 // picked for the FP32 cores; the symmetric contractions likewise.
@@ -149,7 +160,7 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // without cut tiles, which need no scratch, where eight rounds of them
         // hide the last one (8192 x 1024: 0.518 ms against 0.508; 6500 x 1500
         // 0.437 and 0.408).
-        if (M >= 2048 && K < 160) return 16;
+        if (K < kSplitMinSum || (M >= 2048 && K < 160)) return 16;
         // (up to order 64 from rank 200 on for its smaller error: 33 x 231 5.6e-8
         // against 8.8e-8 in 32 x 32 tiles, rms)
         if (M <= 640 && K >= (M <= 64 ? 200 : 400) && K < 1000) return 9;
@@ -165,6 +176,7 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // predicted work for each problem).  Class 0 (128 x 128)
         // where its padding is small (24 + 24 problems from 700 to 2500:
         // 1.49 ms, all in class 1 1.72; from 500 to 1200 0.371 and 0.382).
+        if (K < kSplitMinSum) return 3;
         return M >= 768 && N >= 768 && K >= 256 ? 0 : 1;
     }
     if (kernel == LI_KERNEL_GEMM_LP || kernel == LI_KERNEL_GEMM_LP_SPLIT) {
