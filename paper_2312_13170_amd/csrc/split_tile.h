@@ -29,11 +29,23 @@
 // bf16 cores then execute 1.29 PFLOP/s, what a large bf16 product of the
 // vendor library reaches on this card (power-limited clock).
 //
-// Elements that the three parts cannot hold are noticed: a third part with
-// bits below bf16's (magnitudes of about 2^-110 and less) while splitting,
-// infinities and NaN, values that round to infinity as bf16, and sums that
-// left the finite range, by the NaN or infinity they leave in the block tile.  The block tile is then reduced
-// again on the FP32 cores, so every input gives what they give.
+// Range.  An infinity or NaN of an operand is one in its first part, so the
+// leading sum alone is then what the FP32 cores give (x0*y0 has the sign of
+// x*y, and is NaN where x*y is), and the second accumulator, which mixes in
+// products of infinity and zero parts, is left out of such results.  Three
+// things need the FP32 cores: values that round to infinity as bf16, sums
+// that leave the finite range, and third parts with bits below bf16's last
+// one, 2^-133, which magnitudes of about 2^-110 and less may have (noticed
+// while splitting).  A block tile that holds a result that is not finite, or
+// that lost bits, reads its operands once more: it is reduced again on the
+// FP32 cores where a finite operand of 2^62 / sqrt(k) or more may be why the
+// result is not finite, or where the lost bits, at most 2^-133 of each
+// element, may count in a result (reduce_again).  So every input gives what
+// the FP32 cores give.  2048^3, 90 us: 126 us with a NaN in every row, 134
+// with a hundredth of A below 1e-36, 248 where every tile is reduced again
+// (results of 1e-35); the FP32 cores take 130.  (A scale of 2^16 on both operands, which brings
+// every small value into the parts' range, is one product per element: 1.5%
+// at 8192^3, 4% where the splitting bounds the tile, syrk 768 x 704.)
 //
 // Work split.  Splitting is paid once per element and block tile: PW
 // splitting waves load the next K-tiles from memory, split them and store
@@ -565,6 +577,66 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
         }
     }
 
+    // This thread's share of an operand's R rows (those of the matrix) and of k
+    // in [kbeg, kend): whether a finite (transformed) value reaches `limit`.
+    template <bool KMAJOR, int R>
+    __device__ __forceinline__ static bool reaches(const float *P, int64_t ld, int64_t rows, int64_t kbeg,
+                                                   int64_t kend, int64_t r0, float limit, const XRegs *xr)
+    {
+        constexpr int KL = KMAJOR ? NT / R : 32, RL = KMAJOR ? R : NT / 32;  // threads over k and over rows
+        static_assert(KL >= 1 && RL >= 1, "threads must cover the rows");
+        const int kt = KMAJOR ? threadIdx.x / RL : threadIdx.x % KL;
+        float most = 0.f;
+        for (int r = KMAJOR ? threadIdx.x % RL : threadIdx.x / KL; r < R && r0 + r < rows && kt < KL; r += RL) {
+            float m = 0.f, f = 1.f;
+            if constexpr (XFORM != 0) m = (float)xr->mean[r0 + r];
+            if constexpr (XFORM == 2) f = (float)xr->factor[r0 + r];
+            const float *p = KMAJOR ? P + r0 + r : P + (r0 + r) * ld;
+#pragma unroll 8
+            for (int64_t k = kbeg + kt; k < kend; k += KL) {
+                const float x = p[KMAJOR ? k * ld : k], y = __builtin_fabsf(XFORM ? (x - m) * f : x);
+                most = __builtin_fmaxf(most, y < __builtin_inff() ? y : 0.f);
+            }
+        }
+        return most >= limit;
+    }
+
+    // Of a tile with results that are not finite (odd) or third parts that
+    // lost bits (lost): whether it has to be reduced on the FP32 cores.  acc:
+    // its results, from the leading sums alone where those are not finite.
+    // Reached by every thread.
+    __device__ __forceinline__ static bool reduce_again(const f32x16 (&acc)[TM][TN], bool odd, bool lost,
+                                                        const float *A, const float *B, const float *A1,
+                                                        const float *B1, int64_t lda, int64_t ldb, int64_t M,
+                                                        int64_t N, int64_t kbeg, int64_t kend, int64_t m0,
+                                                        int64_t n0, const XRegs *xr)
+    {
+        odd = __syncthreads_or(odd);
+        lost = __syncthreads_or(lost);
+        if (odd && lost) return true;
+        const int bits = 64 - __builtin_clzll((uint64_t)(kend - kbeg));
+        // operands below 2^62 / sqrt(k) keep every sum in the finite range;
+        // where bits were lost, operands below 2^32 lose less than k 2^-100 of
+        // a result: nothing of one that is 2^30 times as large
+        const float limit = odd ? __builtin_ldexpf(1.f, 62 - bits / 2) : 0x1p32f;
+        bool again = false;
+        if (lost && active()) {
+            float least = __builtin_inff();
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) least = __builtin_fminf(least, __builtin_fabsf(acc[i][j][v]));
+            again = least < __builtin_ldexpf(1.f, bits - 70);
+        }
+        if (__syncthreads_or(again)) return true;
+        for (int pass = 0; pass < (A1 ? 2 : 1); ++pass)
+            again = again || reaches<A_KMAJOR, BM>(pass ? A1 : A, lda, M, kbeg, kend, m0, limit, xr) ||
+                    reaches<!B_NMAJOR, BN>(pass ? B1 : B, ldb, N, kbeg, kend, n0, limit, xr);
+        return __syncthreads_or(again);
+    }
+
     // acc = A B (+ A1 B1 when A1 is given) over k in [kbeg, kend); acc holds
     // the result in the matrix waves.
     __device__ __forceinline__ static void contract(float *lds, const float *A, const float *B, const float *A1,
@@ -572,31 +644,41 @@ struct SplitTile : F32Tile<BM_, BN_, 32, WM_, WN_, A_KMAJOR, kLoadScalar, 1, B_N
                                                     int64_t N, int64_t kbeg, int64_t kend, int64_t m0, int64_t n0,
                                                     f32x16 (&acc)[TM][TN], const XRegs *xr)
     {
-        uint32_t lost = 0;
-        if (kend > kbeg) {
-            f32x16 lo[TM][TN];
-            Base::zero(acc);
-            Base::zero(lo);
-            uint16_t *l16 = reinterpret_cast<uint16_t *>(lds);
-            reduce(l16, A, A1, lda, B, B1, ldb, M, N, kbeg, kend, m0, n0, acc, lo, lost, xr);
+        if (kend <= kbeg) return;
+        uint32_t bits = 0;
+        f32x16 lo[TM][TN];
+        Base::zero(acc);
+        Base::zero(lo);
+        uint16_t *l16 = reinterpret_cast<uint16_t *>(lds);
+        reduce(l16, A, A1, lda, B, B1, ldb, M, N, kbeg, kend, m0, n0, acc, lo, bits, xr);
+        const bool lost = (bits & 0xffffu) != 0;
+        float x = 0.f;  // (0 * x is 0 for finite x)
+        if (active()) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    lo[i][j] += acc[i][j];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) x = __builtin_fmaf(lo[i][j][v], 0.f, x);
+                }
+        }
+        const bool odd = !(x == 0.f);
+        // (what is rare stands behind the rest: a jump is a wait for instructions)
+        if (__builtin_expect(!__syncthreads_or(odd || lost), 1)) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = lo[i][j];
+        } else {
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    if (DUAL) acc[i][j] += lo[i][j];
-            bool bad = (lost & 0xffffu) != 0;
-            // an infinity or NaN among the sums (0 * x is 0 for finite x)
-            if (active()) {
-                float s = 0.f;
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
-#pragma unroll
-                    for (int j = 0; j < TN; ++j)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) s = __builtin_fmaf(acc[i][j][v], 0.f, s);
-                bad |= !(s == 0.f);
-            }
-            if (__syncthreads_or(bad)) {
+                    for (int v = 0; v < 16; ++v)
+                        acc[i][j][v] = __builtin_isfinite(acc[i][j][v]) ? lo[i][j][v] : acc[i][j][v];
+            if (reduce_again(acc, odd, lost, A, B, A1, B1, lda, ldb, M, N, kbeg, kend, m0, n0, xr)) {
                 Base::zero(acc);
                 reduce_safe(lds, A, lda, B, ldb, M, N, kbeg, kend, m0, n0, acc, xr);
                 if (A1) reduce_safe(lds, A1, lda, B1, ldb, M, N, kbeg, kend, m0, n0, acc, xr);
