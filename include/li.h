@@ -401,9 +401,12 @@ int32_t li_tune_pick(int32_t kernel, int64_t M, int64_t N, int64_t K);
  * search to time each candidate through the ordinary entry points. */
 li_status li_tune_force(int32_t kernel, int32_t index);
 /* Persist / restore the table as text, one "kernel bucket index" line per
- * set entry ('#' starts a comment).  Loading replaces every entry it names
- * and rejects the whole file (changing nothing) if any line is malformed or
- * out of range (LI_ERR_NOT_FOUND if the file cannot be opened). */
+ * set entry ('#' starts a comment).  The first line names the version of the
+ * candidates' numbers; a file without one is of version 1, and where a number
+ * has changed since, its entries get the present number of their shape.
+ * Loading replaces every entry it names and rejects the whole file (changing
+ * nothing) if any line is malformed or out of range or the version is unknown
+ * (LI_ERR_NOT_FOUND if the file cannot be opened). */
 li_status li_tune_save(const char *path);
 li_status li_tune_load(const char *path);
 

@@ -250,7 +250,7 @@ bool shapes_consistent()
 // kind (forced > table > built-in heuristic); rows of `ld` elements that the
 // split tiles' offsets cannot span take the FP32 cores' class.
 constexpr int kFp32Class = 3;
-static_assert(kNumClasses == kFp32Class + 1, "the last class is the FP32 cores'");
+static_assert(kNumClasses > kFp32Class, "the class of the FP32 cores is in the list");
 int pick_class(int kernel, int64_t M, int64_t N, int64_t K, int64_t ld)
 {
     if (ld > kSplitMaxLd) return kFp32Class;

@@ -3,6 +3,10 @@
 // shapes.  The grouped kernels (grouped.hip) check at plan time that the
 // candidates they share with the single-problem kernels have the same shape.
 
+// Numbers stand in saved tables: a new shape is appended, no number gets
+// another one.  (Version 1 of the tables had FP32-core tiles at some that name
+// split tiles now; tune.cpp, kRenumbered, maps them to where those stand.)
+
 // {index, bm, bn, bk, waves_m, waves_n, split_k, prefetch depth}
 // split_k: 1 none, > 1 split reduction into that many chunks, 0 stream-K or,
 // for the split tiles, a plan of phases (symmetric contractions only).
@@ -100,7 +104,10 @@
     X(26, 32, 32, 32, 1, 1, 1, 3)            \
     X(27, 32, 32, 32, 1, 1, 1, 10)           \
     X(28, 128, 128, 32, 2, 2, 1, 9)          \
-    X(29, 64, 64, 32, 2, 2, 1, 9)
+    X(29, 64, 64, 32, 2, 2, 1, 9)            \
+    X(30, 128, 128, 32, 4, 4, 7, 2)          \
+    X(31, 128, 128, 32, 4, 4, 0, 4)          \
+    X(32, 64, 64, 32, 2, 2, 0, 2)
 
 // bf16 / fp16 matrix-core GEMM on pre-rounded operands; the last column is
 // the LDS layout here (1: XOR-swizzled rows, 2: rows padded by 16 bytes,
@@ -163,16 +170,19 @@
     X(14, 64, 64, 32, 2, 2, 0, 9)            \
     X(15, 128, 128, 32, 2, 2, 0, 9)          \
     X(16, 64, 64, 32, 2, 2, 1, 3)            \
-    X(17, 32, 32, 32, 1, 1, 1, 10)
+    X(17, 32, 32, 32, 1, 1, 1, 10)           \
+    X(18, 64, 64, 32, 2, 2, 4, 2)            \
+    X(19, 64, 64, 32, 2, 2, 0, 2)            \
+    X(20, 128, 128, 32, 4, 4, 0, 4)
 
 // Shape classes of the grouped execution (grouped.hip), also the candidates
 // of the tuning families LI_KERNEL_GROUPED_GEMM / LI_KERNEL_GROUPED_COV.
 // Each class is one contraction kernel per problem kind whose tiles share
 // the block tile; all load rows of any alignment with 16-byte loads.
-// Classes 0 to 2 are the split tiles (three bf16 parts), class 3 the FP32
-// cores' tile for short reductions and for rows too long for the split
-// tiles' offsets (mode 3: two K-tiles in flight, the LDS operand reads
-// pipelined across the barrier).  The GEMM and covariance candidates named
+// Classes 0 to 2 are the split tiles (three bf16 parts), 3 to 5 the FP32
+// cores' tiles (mode 3: two K-tiles in flight, the LDS operand reads pipelined
+// across the barrier): 3 for results of a few products and for rows too long
+// for the split tiles' offsets, all three for tables of earlier numbering.  The GEMM and covariance candidates named
 // are the single-problem candidates of the same shape, which the
 // per-instance launch loop of a plan uses.
 // {class, GEMM candidate, covariance candidate, block tile, BK, waves_m,
@@ -182,4 +192,6 @@
     X(0, 51, 28, 128, 32, 2, 2, 9) \
     X(1, 52, 29, 64, 32, 2, 2, 9)  \
     X(2, 55, 27, 32, 32, 1, 1, 10) \
-    X(3, 16, 23, 64, 32, 2, 2, 3)
+    X(3, 16, 23, 64, 32, 2, 2, 3)  \
+    X(4, 13, 22, 128, 32, 2, 4, 3) \
+    X(5, 50, 26, 32, 32, 1, 1, 3)

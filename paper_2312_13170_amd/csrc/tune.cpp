@@ -54,6 +54,28 @@ const TileCfg *family(int k, int *n)
     }
 }
 
+// Version of a saved table, in its first line (none: 1), and the candidates
+// whose shape has another number since a version.
+constexpr int kTableVersion = 2;
+struct Renumbered {
+    int version;  // the last one with the old number
+    int kernel, old_idx, idx;
+};
+const Renumbered kRenumbered[] = {
+    {1, LI_KERNEL_SYRK_F32, 10, 30},    {1, LI_KERNEL_SYRK_F32, 20, 31},    {1, LI_KERNEL_SYRK_F32, 21, 32},
+    {1, LI_KERNEL_SYRK_ROWS, 9, 18},    {1, LI_KERNEL_SYRK_ROWS, 10, 16},   {1, LI_KERNEL_SYRK_ROWS, 14, 19},
+    {1, LI_KERNEL_SYRK_ROWS, 15, 20},   {1, LI_KERNEL_GROUPED_GEMM, 0, 4},  {1, LI_KERNEL_GROUPED_GEMM, 1, 3},
+    {1, LI_KERNEL_GROUPED_GEMM, 2, 5},  {1, LI_KERNEL_GROUPED_COV, 0, 4},   {1, LI_KERNEL_GROUPED_COV, 1, 3},
+    {1, LI_KERNEL_GROUPED_COV, 2, 5},
+};
+
+int current_number(int version, int kernel, int idx)
+{
+    for (const Renumbered &r : kRenumbered)
+        if (version <= r.version && kernel == r.kernel && idx == r.old_idx) return r.idx;
+    return idx;
+}
+
 // Entries hold candidate index + 1; the static zero-initialisation therefore
 // means "unset" without any start-up code.
 std::atomic<int> g_table[kFamilies][kBuckets];
@@ -443,7 +465,7 @@ li_status li_tune_save(const char *path)
     if (!path) return li::fail(LI_ERR_NULL_POINTER, "path is NULL");
     FILE *f = fopen(path, "w");
     if (!f) return li::fail(LI_ERR_NOT_FOUND, "cannot write %s", path);
-    fprintf(f, "# li tuning table (gfx950): kernel slot candidate\n");
+    fprintf(f, "# li tuning table (gfx950) version %d: kernel slot candidate\n", li::kTableVersion);
     for (int k = 0; k < li::kFamilies; ++k)
         for (int b = 0; b < li::kBuckets; ++b) {
             const int v = li::g_table[k][b].load() - 1;
@@ -462,13 +484,19 @@ li_status li_tune_load(const char *path)
         int k, b, v;
     };
     Entry entries[li::kFamilies * li::kBuckets];
-    int n = 0, line_no = 0;
+    int n = 0, line_no = 0, version = 1;
     char line[256];
     li_status st = LI_OK;
     while (st == LI_OK && fgets(line, sizeof(line), f)) {
         ++line_no;
         char *p = line;
         while (*p == ' ' || *p == '\t') ++p;
+        if (n == 0 && sscanf(p, "# li tuning table (gfx950) version %d", &version) == 1 &&
+            (version < 1 || version > li::kTableVersion)) {
+            st = li::fail(LI_ERR_INVALID_SIZE, "%s:%d: table version %d, this library knows 1 to %d", path, line_no,
+                          version, li::kTableVersion);
+            break;
+        }
         if (*p == '#' || *p == '\n' || *p == '\r' || *p == 0) continue;
         int k, b, v, cnt;
         if (sscanf(p, "%d %d %d %n", &k, &b, &v, &cnt) != 3 || (p[cnt] != 0 && p[cnt] != '#')) {
@@ -480,7 +508,7 @@ li_status li_tune_load(const char *path)
             st = li::fail(LI_ERR_INVALID_SIZE, "%s:%d: entry out of range", path, line_no);
             break;
         }
-        if (n < li::kFamilies * li::kBuckets) entries[n++] = {k, b, v};
+        if (n < li::kFamilies * li::kBuckets) entries[n++] = {k, b, li::current_number(version, k, v)};
     }
     fclose(f);
     if (st != LI_OK) return st;
