@@ -52,6 +52,7 @@ int tune_key(int kernel, int64_t M, int64_t N, int64_t K);
 // tile are 32-bit byte offsets (256 rows, or 64 k values, of this many
 // elements).
 constexpr int64_t kSplitMaxLd = (int64_t)1 << 21;
+int long_rank_pick(int64_t n);  // candidate of a rank update with longer rows, order n
 double split_gemm_us(int64_t M, int64_t N, int64_t K);  // predicted time of the FP32 product's split tiles
 int tune_pick(int kernel, int64_t M, int64_t N, int64_t K);
 

@@ -13,9 +13,6 @@
 
 namespace li {
 
-// a stream-K candidate of the FP32 cores (the workspace fits any candidate)
-constexpr int kSymRowsPlain = 12;
-
 size_t sym_rows_split_bytes(int64_t n)
 {
     size_t best = 0;
@@ -30,8 +27,9 @@ int launch_sym_rows(int cfg, int64_t n, int64_t k, float alpha, const float *A, 
     const bool two = B != nullptr;
     const bool v4 = k % 4 == 0 && ((uintptr_t)A & 15) == 0 && (!two || ((uintptr_t)B & 15) == 0);
     const SymArgs a{A, B, k, n, k, C, 2, alpha, beta, alpha != 0.f && k > 0 ? 1 : 0, nullptr, nullptr};
-    // (rows too long for the split tiles' 32-bit offsets)
-    if (k > kSplitMaxLd) cfg = kSymRowsPlain;
+    // (rows too long for a forced or table's split tile; the workspace fits
+    // any candidate)
+    if (k > kSplitMaxLd && tune_cfg(LI_KERNEL_SYRK_ROWS, cfg).prefetch >= 9) cfg = long_rank_pick(n);
     switch (cfg) {
 #define LI_RUN(BM, BN, BK, WM, WN, SK, PF, FORM) \
     run_sym_candidate<BM, BN, BK, WM, WN, PF, PF, false, 0, FORM>(a, v4, true, SK, split_ws, s)

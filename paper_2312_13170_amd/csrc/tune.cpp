@@ -182,6 +182,7 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // without cut tiles, which need no scratch, where eight rounds of them
         // hide the last one (8192 x 1024: 0.518 ms against 0.508; 6500 x 1500
         // 0.437 and 0.408).
+        if (K > kSplitMaxLd) return long_rank_pick(M);
         if (K < kSplitMinSum || (M >= 2048 && K < 160)) return 16;
         // (up to order 64 from rank 200 on for its smaller error: 33 x 231 5.6e-8
         // against 8.8e-8 in 32 x 32 tiles, rms)
@@ -210,6 +211,17 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
 }
 
 }  // namespace
+
+// Rank updates whose rows are too long for the split tiles: stream-K on the
+// FP32 cores, in 64 x 64 tiles where these leave enough of the 128 x 128
+// tiles' padding out to make up for their cost of 1.3 times per element (rank
+// 2097157, syrk, 64 x 64 and 128 x 128: order 33 0.33 and 0.61 ms, 100 0.66
+// and 0.66, 200 1.84 and 1.74, 300 2.87 and 3.30, 600 10.5 and 8.6).
+int long_rank_pick(int64_t n)
+{
+    const int64_t t64 = ceil_div(n, 64), t128 = ceil_div(n, 128);
+    return 1.3 * (double)(t64 * (t64 + 1)) < 4.0 * (double)(t128 * (t128 + 1)) ? 19 : 20;
+}
 
 double split_gemm_us(int64_t M, int64_t N, int64_t K)
 {

@@ -22,3 +22,17 @@ def test_sums_of_few_products(li):
                 assert not split(li, family, M, M, K), (family, M, K)
     assert split(li, li.LI_KERNEL_SYRK_ROWS, 64, 64, 4)
     assert split(li, li.LI_KERNEL_GROUPED_GEMM, 64, 64, 4)
+
+
+def test_long_ranks(li):
+    # rows too long for the split tiles: FP32 stream-K in 64 x 64 tiles where
+    # they leave padding out; what is forced stands
+    R, K = li.LI_KERNEL_SYRK_ROWS, 2 ** 21 + 1
+    for n, tile in ((1, 64), (64, 64), (96, 64), (200, 128), (300, 64), (600, 128), (5000, 128)):
+        c = li.li_tune_candidate(R, li.li_tune_pick(R, n, n, K))
+        assert (c["bm"], c["split_k"]) == (tile, 0) and c["prefetch"] < 9, n
+    try:
+        li.li_tune_force(R, 7)
+        assert li.li_tune_pick(R, 300, 300, K) == 7
+    finally:
+        li.li_tune_force(R, -1)
