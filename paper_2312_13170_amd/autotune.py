@@ -8,7 +8,9 @@ candidate is written to the table (li_tune_set) and the table is saved as
 text (li_tune_save), which li.py loads at import.  The table that comes with
 the library has entries for the 16-bit products only: the FP32 products, the
 symmetric contractions and the batches go by the measured rules of
-csrc/tune.cpp, which searched entries would override.
+csrc/tune.cpp, which searched entries override (an entry of the FP32 products
+holds for every reduction length of its output size).  They are searched only
+when --only names them.
 
 Representative problems per table slot (li_tune_key:
 the GEMM families key by the output's area, which for the square problems
@@ -23,7 +25,7 @@ sizes drawn log-uniform inside the bucket (32 to 1024, the batch's range):
 each class is forced while the plan is built and the graph launch is
 timed.
 
-Usage: python -m paper_2312_13170_amd.autotune [--out PATH] [--quick]
+Usage: python -m paper_2312_13170_amd.autotune [--out PATH] [--quick] [--only FAMILIES]
 """
 import argparse
 import json
@@ -177,15 +179,24 @@ def search_grouped(kernel, kind, buckets, reps, log, passes=2):
         del keep
 
 
-def main():
+# the families whose choices the table holds; those of the others are rules
+DEFAULT_FAMILIES = "lp"
+
+
+def parser():
     p = argparse.ArgumentParser()
     p.add_argument("--out", default=os.path.join(HERE, "tune_gfx950.txt"))
     p.add_argument("--log", default=None, help="also write the timings as JSON lines")
     p.add_argument("--quick", action="store_true", help="fewer sizes and repetitions")
-    p.add_argument("--only", default="gemm,syrk,rows,lp,grouped",
+    p.add_argument("--only", default=DEFAULT_FAMILIES,
                    help="comma list of the families to search (gemm, syrk, rows, lp, grouped); "
-                        "the table's other entries are kept as loaded")
-    a = p.parse_args()
+                        "the table's other entries are kept as loaded, and searched entries of "
+                        "the others than lp override the measured rules (default: %(default)s)")
+    return p
+
+
+def main():
+    a = parser().parse_args()
     only = set(a.only.split(","))
     torch.cuda.set_device(0)
     li.li_init()

@@ -72,3 +72,14 @@ def test_unknown_version_is_refused(li, tmp_path):
     with pytest.raises(li.LiError):
         li.li_tune_load(str(path))
     assert li.li_tune_get(1, 30) == before
+
+
+def test_default_search_keeps_the_rules(li):
+    # the shipped table and the default search hold the same families, so that
+    # a search does not write over the rules of the others
+    import os
+    from paper_2312_13170_amd import autotune
+    assert autotune.parser().parse_args([]).only == "lp"
+    table = os.path.join(os.path.dirname(autotune.__file__), "tune_gfx950.txt")
+    lines = [l.split() for l in open(table) if l.strip() and not l.startswith("#")]
+    assert {int(l[0]) for l in lines} == {li.LI_KERNEL_GEMM_LP, li.LI_KERNEL_GEMM_LP_SPLIT}
