@@ -184,9 +184,13 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // 0.437 and 0.408).
         if (K > kSplitMaxLd) return long_rank_pick(M);
         if (K < kSplitMinSum || (M >= 2048 && K < 160)) return 16;
-        // (up to order 64 from rank 200 on for its smaller error: 33 x 231 5.6e-8
-        // against 8.8e-8 in 32 x 32 tiles, rms)
-        if (M <= 640 && K >= (M <= 64 ? 200 : 400) && K < 1000) return 9;
+        // Small orders are split in four from rank 200 on for the error: uncut,
+        // a 32 x 32 tile's depends on the rank alone (rms 8.8e-8 at 231, 9.4e-8
+        // at 300, 1.03e-7 at 379), the FP32 cores' tile that it replaces was
+        // cut in four and its error falls with the order (231 / 300 / 379:
+        // order 100 0.99 / 1.15 / 1.10e-7, 80 0.97 / 1.11 / 1.02, 48 0.90 /
+        // 1.02 / 0.93, 16 0.80 / 0.88 / 0.82; here cut 4.7 to 5.3e-8).
+        if (M <= 640 && K >= (M <= 96 ? 200 : 400) && K < 1000) return 9;
         if (M <= 1152 && K < 700) return 17;
         if (M >= 8192 && 4 * K < 3 * M) return 10;
         return K >= 640 && (double)M * (double)M * (double)K >= 2.5e9 ? 15 : 14;

@@ -104,3 +104,95 @@ def test_single_products(li, values):
         assert np.all(np.abs(out - q) <= BOUND * np.abs(q)), cfg
         out = rank_update(li, cfg, a[:, None], c)
         assert np.all(np.abs(out - (p + p.T)) <= (BOUND + 2.0 ** -24) * (np.abs(p) + np.abs(p.T))), cfg
+
+
+# Sums: in every form the split tiles are no further from 64 bits (rms) than
+# the FP32 cores' uncut tile, on operands with all 24 bits.
+def rms(x, ref):
+    return float(np.sqrt(np.mean((x - ref) ** 2)))
+
+
+def fp32_uncut(li, family):
+    for i in range(li.li_tune_num_candidates(family)):
+        c = li.li_tune_candidate(family, i)
+        if c["prefetch"] < 9 and c["split_k"] == 1:
+            return i
+
+
+@pytest.mark.parametrize("n,k", [(40, 64), (150, 333), (300, 2100)])
+def test_sums_of_rank_updates(li, n, k):
+    A, B = synth.uniform_pm1(192, "A", (n, k)), synth.uniform_pm1(192, "B", (n, k))
+    a, b = A.astype(np.float64), B.astype(np.float64)
+    for z, ref in ((None, a @ a.T), (B, a @ b.T + b @ a.T)):
+        most = rms(rank_update(li, fp32_uncut(li, li.LI_KERNEL_SYRK_ROWS), A, z), ref)
+        for cfg in split_candidates(li, li.LI_KERNEL_SYRK_ROWS):
+            say("rank update sums", (n, k, z is None), "candidate", cfg)
+            assert rms(rank_update(li, cfg, A, z), ref) <= most, (z is None, cfg)
+
+
+@pytest.mark.parametrize("n", [16, 48, 64, 96, 130, 250])
+@pytest.mark.parametrize("k", [150, 231, 379, 650])
+def test_picks_of_rank_updates(li, n, k):
+    # the rule's choice against the FP32 cores' 64 x 64 tile split in four;
+    # several inputs, as both errors are small samples
+    four = next(i for i in range(li.li_tune_num_candidates(li.LI_KERNEL_SYRK_ROWS))
+                if li.li_tune_candidate(li.LI_KERNEL_SYRK_ROWS, i)["prefetch"] < 9 and
+                li.li_tune_candidate(li.LI_KERNEL_SYRK_ROWS, i)["bm"] == 64 and
+                li.li_tune_candidate(li.LI_KERNEL_SYRK_ROWS, i)["split_k"] == 4)
+    e = np.zeros(2)
+    say("rank update pick", n, k)
+    for seed in range(8):
+        A = synth.uniform_pm1(300 + seed, "A", (n, k))
+        ref = A.astype(np.float64) @ A.astype(np.float64).T
+        e += [rms(rank_update(li, -1, A), ref), rms(rank_update(li, four, A), ref)]
+    assert e[0] <= e[1]
+
+
+@pytest.mark.parametrize("n,k", [(40, 300), (150, 1100), (300, 4200)])
+def test_sums_of_statistics(li, n, k):
+    X = synth.uniform_pm1(193, "X", (k, n)) + np.float32(0.25)
+    x = X.astype(np.float64)
+    x = x - x.mean(0)
+    y = x / (np.sqrt(k) * np.sqrt((x ** 2).mean(0)))
+    dX = dev(X)
+    mean, sd = (torch.empty(n, dtype=torch.float64, device="cuda") for _ in range(2))
+    ws = torch.empty(li.li_stats_workspace_bytes(n, k), dtype=torch.uint8, device="cuda")
+
+    def run(cfg, corr, fused):
+        out = empty((n, n), fill=float("nan"))
+        with Forced(li, li.LI_KERNEL_SYRK_F32, cfg):
+            if corr and fused:
+                li.li_correlation_fused(n, k, 0.0, dX, mean, sd, out, ws)
+            elif corr:
+                li.li_correlation(n, k, 0.0, dX, empty((k, n)), mean, sd, out, ws)
+            elif fused:
+                li.li_covariance_fused(n, k, dX, mean, out, ws)
+            else:
+                li.li_covariance(n, k, dX, empty((k, n)), mean, out, ws)
+        return host(out)
+
+    for corr in (False, True):
+        ref = y.T @ y if corr else x.T @ x / (k - 1)
+        for fused in (False, True):
+            most = rms(run(fp32_uncut(li, li.LI_KERNEL_SYRK_F32), corr, fused), ref)
+            for cfg in split_candidates(li, li.LI_KERNEL_SYRK_F32):
+                say("statistics sums", (n, k, corr, fused), "candidate", cfg)
+                assert rms(run(cfg, corr, fused), ref) <= most, (corr, fused, cfg)
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 1024), (300, 200, 4100), (1100, 1300, 1030)],
+                         ids=lambda s: "%dx%dx%d" % s)
+def test_sums_of_products(li, shape):
+    M, N, K = shape
+    A, B = synth.uniform_pm1(194, "A", (M, K)), synth.uniform_pm1(194, "B", (K, N))
+    ref = A.astype(np.float64) @ B.astype(np.float64)
+    most = rms(gemm(li, fp32_uncut(li, li.LI_KERNEL_GEMM_F32), A, B), ref)
+    need = li.li_gemm_ex_workspace_bytes(M, N, K, "fp32")
+    assert need > 0
+    say("products with a workspace", shape)
+    C = empty((M, N), fill=float("nan"))
+    li.li_gemm_ex(M, N, K, 1.0, dev(A), dev(B), 0.0, C, "fp32", empty((need // 4 + 1,), fill=float("nan")))
+    assert rms(host(C), ref) <= most
+    for cls in split_candidates(li, li.LI_KERNEL_GROUPED_GEMM):
+        say("batch sums", shape, "class", cls)
+        assert rms(grouped(li, cls, A, B), ref) <= most, cls

@@ -36,3 +36,14 @@ def test_long_ranks(li):
         assert li.li_tune_pick(R, 300, 300, K) == 7
     finally:
         li.li_tune_force(R, -1)
+
+
+def test_small_orders_are_cut(li):
+    # rank updates of small orders: split in four from rank 200 on, as the
+    # FP32 cores' tile before them
+    R = li.LI_KERNEL_SYRK_ROWS
+    for n in (1, 33, 64, 65, 96):
+        assert li.li_tune_candidate(R, li.li_tune_pick(R, n, n, 199))["split_k"] == 1
+        for k in (200, 379, 999):
+            assert li.li_tune_candidate(R, li.li_tune_pick(R, n, n, k))["split_k"] == 4, (n, k)
+    assert li.li_tune_candidate(R, li.li_tune_pick(R, 97, 97, 399))["split_k"] == 1
