@@ -355,9 +355,14 @@ int launch_gemm_f32_streamk(int64_t M, int64_t N, int64_t K, float alpha, const 
         const double plain = split_gemm_us(M, N, K);
         const double t128 = 1.18 * phase_us<PhaseTile128>(M, N, K) + 5.0;
         const double t64 = 1.02 * phase_us<PhaseTile64>(M, N, K) + 6.0;
-        // Few tiles: always cut, as stream-K did (it summed a small output in
-        // up to 256 ranges, 330 x 448 x 1472 with an rms error of 1.8e-7;
-        // uncut, the split tiles' is 2.1e-7).
+        // Few tiles: always cut, for the error.  Stream-K on the FP32 cores,
+        // which took these calls before, cuts each of the fewer tiles into
+        // more ranges (rms at K = 1024 / 2000 / 4096: 1 tile 1.5e-7 / 1.8 / 2.3,
+        // 16 1.6 / 2.2 / 3.0, 24 1.9 / 2.5 / 3.5, 40 2.3 / 3.2 / 4.5); uncut
+        // split tiles have 1.7 / 2.5 / 3.7 whatever their number, cut ones 0.9 /
+        // 1.0 / 1.0 with 1 and 1.2 / 1.7 / 1.2 with 24.  Only calls of 12 to 16
+        // tiles and K below 1200 would be faster uncut (512 x 512 x 1024: 11.2 us
+        // against 13.2).
         const bool few = p.nb < 32;
         if ((few || t128 < plain) && t128 <= t64)
             return run_gemm_phases<PhaseTile128>(M, N, K, alpha, A, B, beta, C, ws, s);

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kStatThreads) void colstats_partial(const float *__
 // the weights, two FP64 divisions a merge, are the same for every column (and
 // group, but for a short last chunk), so each thread computes one pair for
 // all, and a batch of partials is loaded while the one before is merged (501
-// columns, 1001 chunks: 18.6 -> 11.1 us; 64 columns, 2000 chunks: 25.8 -> 14.4).
+// columns, 626 chunks: 18.6 -> 11.1 us; 64 columns, 1000 chunks: 25.8 -> 14.4).
 constexpr int kFinCols = kStatThreads / kMergeGroups;
 constexpr int kFinBatch = 16;
 

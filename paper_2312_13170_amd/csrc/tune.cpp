@@ -361,26 +361,26 @@ int refine(const QuantCand (&list)[NQ], const TileCfg *fam, double min_side, int
     return quant_time(fam[cur->idx], cur->cost, M, N) > 1.05 * tbest ? best->idx : t;
 }
 
-// Split reductions of the covariance contraction launch (upper-triangle
-// tiles) x (chunks) work-groups, each writing a partial tile.  The table's
-// split choices are searched where that count fits in one round of the
+// Only a table's entry gets here: the rules above name no tile split in a
+// fixed number.  Split reductions of the covariance contraction launch
+// (upper-triangle tiles) x (chunks) work-groups, each writing a partial tile.
+// Split choices are searched where that count fits in one round of the
 // 256 compute units; at the top of the same slot (orders up to twice as
 // large) it spills into a second or later round, and with short chunks
 // the partial tiles' traffic weighs as much as the products: there the
-// stream-K schedule of the same tile (balanced ranges, no idle round) is
-// faster (1500 features x 3000 samples: 0.123 ms split in seven, 0.095 ms
-// stream-K; 1900 x 5000 and 1800 x 3600 alike).  Chunks of 4096 and more
+// phases of the split tile of the same size are faster (times with the
+// statistics, FP32 cores in seven / split tile in seven / phases: 1500 features
+// x 3000 samples 121 / 93 / 71 us, 1900 x 5000 234 / 174 / 142, 1800 x 3600
+// 181 / 138 / 108; FP32 stream-K 96, 196, 148).  Chunks of 4096 and more
 // amortise their partial tile.  The row-form updates keep their table
-// entries: their 64 x 64 split in four stays ahead of stream-K at order
-// 900 (480 work-groups), and no spilled case measured favours the switch
-// by more than a few per cent.
+// entries.
 int refine_cov_split(int t, int64_t M, int64_t K)
 {
     const TileCfg &c = kSyrkF32[t];
     if (c.split_k <= 1) return t;
     const int64_t tt = ceil_div(M, c.bm), up = tt * (tt + 1) / 2;
     if (up * c.split_k <= 256 || K / c.split_k >= 4096) return t;
-    return c.bm == 128 ? 20 : 21;  // stream-K on the same tile
+    return c.bm == 128 ? 20 : 21;  // phases
 }
 
 int tune_pick(int kernel, int64_t M, int64_t N, int64_t K)
