@@ -14,10 +14,11 @@
 //                            main loop and epilogue as the single-problem
 //                            kernels with the tile shape chosen for its
 //                            problem: the split tiles of split_tile.h, or
-//                            the FP32 cores' for rows too long for them.
+//                            the FP32 cores' for rows too long for them and
+//                            for results of few products.
 //
 // 512 products and 512 covariances, sizes log-uniform from 32 to 1024: 868 us
-// on the FP32 cores, 707 on the split tiles.  The three kernels each fill the
+// on the FP32 cores, 720 on the split tiles.  The three kernels each fill the
 // compute units, so their times add (statistics 135, products 330,
 // covariances 330 us): the statistics are near the copy rate (0.6 GB); a
 // product's 64 x 64 tile takes 14 us for 9 K-tiles on average, half of it

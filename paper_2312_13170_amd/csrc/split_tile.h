@@ -24,9 +24,9 @@
 //
 // Why: six bf16 products still run 2.6 times as fast as one on the FP32
 // cores (2.5 PFLOP/s / 6 against 157 TFLOP/s).  Measured (li_gemm, beta != 0,
-// FP32 cores before): 2048^3 0.130 -> 0.088 ms, 8192^3 7.8 -> 5.1 ms,
-// 1531 x 1027 x 777 38.5 -> 24.4 us, 512^3 12.8 -> 8.1 us.  At 8192^3 the
-// bf16 cores then execute 1.29 PFLOP/s, what a large bf16 product of the
+// FP32 cores before): 2048^3 0.130 -> 0.088 ms, 8192^3 7.8 -> 5.2 to 5.4 ms,
+// 1531 x 1027 x 777 38.5 -> 23.2 us, 512^3 12.8 -> 7.8 us.  At 8192^3 the
+// bf16 cores then execute 1.25 PFLOP/s, near what a large bf16 product of the
 // vendor library reaches on this card (power-limited clock).
 //
 // Range.  An infinity or NaN of an operand is one in its first part, so the
