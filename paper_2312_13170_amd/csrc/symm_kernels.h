@@ -211,7 +211,8 @@ __device__ __forceinline__ void finish_sym_block(f32x16 &acc, int i, int j, int 
                                                  int64_t m0, int64_t n0)
 {
     fused_shift_correct_block<T>(acc, i, j, a, m0, n0, vtid);
-    epilogue_syrk_block<T>(acc, i, j, a.S, a.n, m0, n0, a.mode, a.scale, a.beta, vtid);
+    const f32x16 block[1][1] = {{acc}};
+    epilogue_syrk<T>(block, a.S, a.n, m0, n0, a.mode, a.scale, a.beta, vtid, i, j);
 }
 
 // Raw accumulators of one tile as a partial result: BM * BN floats, laid out

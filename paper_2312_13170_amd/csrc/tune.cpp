@@ -181,9 +181,15 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // 108 and 126; 1024 x 1024 21.5 and 20.7; 4096 x 512 101 and 81), or
         // without cut tiles, which need no scratch, where eight rounds of them
         // hide the last one (8192 x 1024: 0.518 ms against 0.508; 6500 x 1500
-        // 0.437 and 0.408).
+        // 0.437 and 0.408; not with a shorter rank: 10000 x 161 0.42 ms whole,
+        // 0.29 in 64 x 64 phases).
         if (K > kSplitMaxLd) return long_rank_pick(M);
-        if (K < kSplitMinSum || (M >= 2048 && K < 160)) return 16;
+        // Very short ranks on the FP32 cores as well, which have no pipeline
+        // of K-tiles to fill (kernels alone, us, FP32 cores' 64 x 64 tile and
+        // the split pick: syrk 1300 x 16 7.6 and 8.8, 1800 x 32 9.6 and 10.4, 1000
+        // x 16 7.0 and 7.8; 1000 x 48 8.1 and 8.4, 1500 x 64 10.1 and 9.2).
+        if (K < kSplitMinSum || (M > 512 && K < (M > 1152 ? 64 : 40) && M < 2048)) return 1;
+        if (M >= 2048 && K < 160) return 16;
         // Small orders are split in four from rank 200 on for the error: uncut,
         // a 32 x 32 tile's depends on the rank alone (rms 8.8e-8 at 231, 9.4e-8
         // at 300, 1.03e-7 at 379), the FP32 cores' tile that it replaces was
@@ -192,7 +198,7 @@ int heuristic(int kernel, int64_t M, int64_t N, int64_t K)
         // 1.02 / 0.93, 16 0.80 / 0.88 / 0.82; here cut 4.7 to 5.3e-8).
         if (M <= 640 && K >= (M <= 96 ? 200 : 400) && K < 1000) return 9;
         if (M <= 1152 && K < 700) return 17;
-        if (M >= 8192 && 4 * K < 3 * M) return 10;
+        if (M >= 8192 && K >= 640 && 4 * K < 3 * M) return 10;
         return K >= 640 && (double)M * (double)M * (double)K >= 2.5e9 ? 15 : 14;
     }
     if (kernel == LI_KERNEL_GROUPED_GEMM || kernel == LI_KERNEL_GROUPED_COV) {

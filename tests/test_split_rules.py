@@ -47,3 +47,15 @@ def test_small_orders_are_cut(li):
         for k in (200, 379, 999):
             assert li.li_tune_candidate(R, li.li_tune_pick(R, n, n, k))["split_k"] == 4, (n, k)
     assert li.li_tune_candidate(R, li.li_tune_pick(R, 97, 97, 399))["split_k"] == 1
+
+
+def test_short_ranks(li):
+    # ranks that fill no pipeline of K-tiles stay on the FP32 cores; a large
+    # result of a middling rank is not taken by whole 128 x 128 tiles
+    R = li.LI_KERNEL_SYRK_ROWS
+    for n, k in ((600, 39), (1000, 16), (1300, 63), (2047, 20), (2048, 100), (8192, 159)):
+        assert not split(li, R, n, n, k), (n, k)
+    for n, k in ((512, 16), (1000, 40), (1300, 64), (2048, 160)):
+        assert split(li, R, n, n, k), (n, k)
+    for n, k in ((8192, 200), (10000, 161), (10000, 639)):
+        assert li.li_tune_candidate(R, li.li_tune_pick(R, n, n, k))["split_k"] == 0, (n, k)
