@@ -96,6 +96,11 @@ li_status validate_gemm(int64_t M, int64_t N, int64_t K, float alpha, const floa
     return LI_OK;
 }
 
+// The reduction that a call with this alpha runs, for the choice of its tile:
+// without one, C = beta C only reads and writes C, and the split tiles' large
+// work-groups are in its way (3000 x 3000: 18.4 us, 11.9 on the FP32 cores').
+int64_t reduction(float alpha, int64_t K) { return alpha != 0.f ? K : 0; }
+
 li_status launched(int err, const char *what)
 {
     if (err != 0) return li::hip_fail(err, what);
@@ -165,7 +170,7 @@ li_status li_gemm_ex(int64_t M, int64_t N, int64_t K, float alpha, const float *
         return launched(li::launch_gemm_f32_streamk(M, N, K, alpha, A, B, beta, C, (float *)workspace, stream),
                         "gemm_f32 stream-K launch");
     if (!lp) {
-        const int cfg = li::tune_pick(LI_KERNEL_GEMM_F32, M, N, K);
+        const int cfg = li::tune_pick(LI_KERNEL_GEMM_F32, M, N, reduction(alpha, K));
         return launched(li::launch_gemm_f32(cfg, M, N, K, alpha, A, K, B, N, beta, C, N, stream),
                         "gemm_f32 launch");
     }
@@ -221,7 +226,7 @@ li_status li_mm2(int64_t NI, int64_t NJ, int64_t NK, int64_t NL, float alpha, fl
         return s;
     if ((s = li::ensure_device())) return s;
     if (NI > 0 && NJ > 0) {
-        const int cfg = li::tune_pick(LI_KERNEL_GEMM_F32, NI, NJ, NK);
+        const int cfg = li::tune_pick(LI_KERNEL_GEMM_F32, NI, NJ, reduction(alpha, NK));
         if ((s = launched(li::launch_gemm_f32(cfg, NI, NJ, NK, alpha, A, NK, B, NJ, 0.f, tmp, NJ, stream),
                           "mm2 first product launch")))
             return s;
@@ -326,7 +331,7 @@ li_status rank_update(int64_t N, int64_t K, float alpha, const float *A, const f
         return s;
     if ((s = li::ensure_device())) return s;
     if (N == 0) return LI_OK;
-    const int cfg = li::tune_pick(LI_KERNEL_SYRK_ROWS, N, N, K);
+    const int cfg = li::tune_pick(LI_KERNEL_SYRK_ROWS, N, N, reduction(alpha, K));
     return launched(li::launch_sym_rows(cfg, N, K, alpha, A, two ? B : nullptr, beta, C, (float *)ws, stream),
                     two ? "syr2k launch" : "syrk launch");
 }

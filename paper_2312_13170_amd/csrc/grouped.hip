@@ -468,7 +468,8 @@ li_status li_group_plan_create(const li_problem *problems, int32_t count, li_gro
         g.mean = q.mean;
         int cls;
         if (q.kind == LI_PROBLEM_GEMM) {
-            cls = pick_class(LI_KERNEL_GROUPED_GEMM, q.M, q.N, q.K, std::max(q.K, q.N));
+            // (no reduction without alpha)
+            cls = pick_class(LI_KERNEL_GROUPED_GEMM, q.M, q.N, q.alpha != 0.f ? q.K : 0, std::max(q.K, q.N));
             const int bt = kClasses[cls].bt;
             g.cfg = kClasses[cls].gemm_idx;
             g.vec4 = (q.alpha == 0.f || (q.K % 4 == 0 && q.N % 4 == 0 && aligned16(q.A) && aligned16(q.B))) ? 1 : 0;

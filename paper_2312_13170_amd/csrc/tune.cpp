@@ -125,7 +125,10 @@ int split_pick(int64_t M, int64_t N, int64_t K, double *predicted = nullptr)
 // Shorter reductions stay on the FP32 cores: a split tile starts with two
 // K-tiles on their way through its pipeline (7001 x 5458 x 94: 105 us against
 // 123 on the best split tile, 1463 x 1664 x 64: 9.0 against 10.1; 1168 x 1600
-// x 126: 10.6 against 9.4, from K = 120 never behind by more than 3%).
+// x 126: 10.6 against 9.4).  From K = 120 on the split tiles are ahead or
+// within 3%, but for some large outputs up to K = 150, which they keep for
+// their error (4096 x 4096 x 128: 58.5 us against 53.7 with beta, 42.2 and 44.2
+// without; 8192 x 8192 x 128: 207 and 219, 181 and 167).
 constexpr int64_t kSplitMinK = 120;
 
 // Results of fewer products than this stay on the FP32 cores wherever the
